@@ -102,9 +102,9 @@ static void carve(Ctx *c, Arena &A, const HostTables &T, const PartTables &PT) {
     c->g.nbr16 = (const unsigned *)ints(T.nbr16.size());
     c->g.blk_nbr = ints(T.blk_nbr.size());
     c->g.plane_start = ints(MAX_PLANES + 1);  // room for any sub-block shape of this block
-    c->g.slot_lex = ints(T.slot_lex.size());
+    c->g.slot_off = ints(T.slot_off.size());
     c->slot_perm = ints(T.slot_lex.size());
-    c->g.blk_lex = ints(T.blk_lex.size());
+    c->g.blk_off = ints(T.blk_off.size());
     c->g.lex_blk = ints(T.lex_blk.size());
     c->g.zord_blk = ints(T.zord_blk.size());
     c->U64 = (double2 *)A.take((size_t)V * 24 * 16);
@@ -341,11 +341,7 @@ int sapq_create(const sapq_geom *geom, const sapq_params *params, void *arena, s
     c->g.NBc = T.NB / 2;
     c->g.V = c->V;
     c->g.nplanes = T.nplanes;
-    for (int m = 0; m < 4; ++m) {
-        c->g.bc[m] = (float)geom->bc_sign[m];
-        c->g.B[m] = geom->block[m];
-        c->g.nbk[m] = T.nbk[m];
-    }
+    for (int m = 0; m < 4; ++m) c->g.bc[m] = (float)geom->bc_sign[m];
     c->red_blocks = RED_BLOCKS;
     c->have_U = c->have_F = false;
     c->n_msap = c->n_d64 = 0;
@@ -353,7 +349,7 @@ int sapq_create(const sapq_geom *geom, const sapq_params *params, void *arena, s
     if (rc) { delete h; return rc; }
     struct { const void *dst; const std::vector<int> *src; } cp[] = {
         {c->g.loc_nbr, &T.loc_nbr}, {c->g.nbr16, &T.nbr16}, {c->g.blk_nbr, &T.blk_nbr}, {c->g.plane_start, &T.plane_start},
-        {c->g.slot_lex, &T.slot_lex}, {c->g.blk_lex, &T.blk_lex}, {c->g.lex_blk, &T.lex_blk}, {c->g.zord_blk, &T.zord_blk}};
+        {c->g.slot_off, &T.slot_off}, {c->g.blk_off, &T.blk_off}, {c->g.lex_blk, &T.lex_blk}, {c->g.zord_blk, &T.zord_blk}};
     for (auto &e : cp) {
         rc = hipcheck(hipMemcpyAsync((void *)e.dst, e.src->data(), e.src->size() * sizeof(int), hipMemcpyHostToDevice, c->stream),
                       "hipMemcpyAsync(tables)");
@@ -592,9 +588,8 @@ int sapq_dk(sapq_ctx *h, double *x, double *w, const double *v) {
     launch_sap_phase(c, 0, true, c->i_tmp, c->sap_r, c->sap_x, c->i_ph);
     launch_sap_phase(c, 1, true, c->i_tmp, c->sap_r, c->sap_x, c->i_ph);
     launch_sap_face(c, 0, c->sap_r, c->sap_x);
-    blas_xpay(c, pi, c->i_v, c->i_tmp, make_double2(-1, 0), c->sap_r);  // w = v - r
     launch_unpack_spinor(c, pi, x, c->sap_x, 1.0);
-    launch_unpack_spinor(c, pi, w, c->i_v, 1.0);
+    launch_unpack_diff(c, pi, w, c->i_tmp, c->sap_r);  // w = v - r
     rc = hipcheck(hipGetLastError(), "sapq_dk");
     return rc ? rc : parts_status(c);
 }
@@ -608,10 +603,7 @@ int sapq_sap_precondition(sapq_ctx *h, double *out, double *d_out, const double 
     launch_pack_spinor(c, pi, c->i_tmp, in, 1.0);
     msap(c, c->i_tmp, c->i_ph);
     launch_unpack_spinor(c, pi, out, c->i_ph, 1.0);
-    if (d_out) {
-        blas_xpay(c, pi, c->i_v, c->i_tmp, make_double2(-1, 0), c->sap_r);
-        launch_unpack_spinor(c, pi, d_out, c->i_v, 1.0);
-    }
+    if (d_out) launch_unpack_diff(c, pi, d_out, c->i_tmp, c->sap_r);
     rc = hipcheck(hipGetLastError(), "sapq_sap_precondition");
     return rc ? rc : parts_status(c);
 }
@@ -677,10 +669,7 @@ int sapq_precondition(sapq_ctx *h, double *out, double *d_out, const double *in)
     launch_pack_spinor(c, pi, c->i_tmp, in, 1.0);
     precondition(c, c->i_tmp, c->i_ph);
     launch_unpack_spinor(c, pi, out, c->i_ph, 1.0);
-    if (d_out) {
-        blas_xpay(c, pi, c->i_v, c->i_tmp, make_double2(-1, 0), c->sap_r);  // D P in = in - r_N
-        launch_unpack_spinor(c, pi, d_out, c->i_v, 1.0);
-    }
+    if (d_out) launch_unpack_diff(c, pi, d_out, c->i_tmp, c->sap_r);  // D P in = in - r_N
     rc = hipcheck(hipGetLastError(), "sapq_precondition");
     return rc ? rc : parts_status(c);
 }
@@ -1102,20 +1091,20 @@ static int apply_subblock(Ctx *c, const int S[4]) {
         return SAPQ_ESHAPE;
     }
     // the packed fields are stored in slot order: re-lay them out for the new order (the
-    // device still holds the old slot -> in-block lexicographic map)
+    // device still holds the old slot -> lexicographic offset map)
     std::vector<int> perm;  // lives until the stream is synchronized below
     if (c->have_U || c->have_F) {
         const int Vb = c->g.Vb;
-        std::vector<int> old_lex(Vb), at(Vb);
+        std::vector<int> old_off(Vb), at(*std::max_element(T.slot_off.begin(), T.slot_off.end()) + 1);
         perm.resize(Vb);
-        rc = hipcheck(hipMemcpyAsync(old_lex.data(), c->g.slot_lex, Vb * sizeof(int), hipMemcpyDeviceToHost, c->stream),
-                      "hipMemcpyAsync(slot_lex)");
+        rc = hipcheck(hipMemcpyAsync(old_off.data(), c->g.slot_off, Vb * sizeof(int), hipMemcpyDeviceToHost, c->stream),
+                      "hipMemcpyAsync(slot_off)");
         if (!rc) rc = hipcheck(hipStreamSynchronize(c->stream), "hipStreamSynchronize");
         if (rc) return rc;
-        for (int s = 0; s < Vb; ++s) at[old_lex[s]] = s;
+        for (int s = 0; s < Vb; ++s) at[old_off[s]] = s;
         bool same = true;
         for (int s = 0; s < Vb; ++s) {
-            perm[s] = at[T.slot_lex[s]];
+            perm[s] = at[T.slot_off[s]];
             same = same && perm[s] == s;
         }
         if (!same) {
@@ -1131,7 +1120,7 @@ static int apply_subblock(Ctx *c, const int S[4]) {
         }
     }
     struct { const void *dst; const std::vector<int> *src; } cp[] = {
-        {c->g.loc_nbr, &T.loc_nbr}, {c->g.nbr16, &T.nbr16}, {c->g.plane_start, &T.plane_start}, {c->g.slot_lex, &T.slot_lex}};
+        {c->g.loc_nbr, &T.loc_nbr}, {c->g.nbr16, &T.nbr16}, {c->g.plane_start, &T.plane_start}, {c->g.slot_off, &T.slot_off}};
     for (auto &e : cp) {
         rc = hipcheck(hipMemcpyAsync((void *)e.dst, e.src->data(), e.src->size() * sizeof(int), hipMemcpyHostToDevice, c->stream),
                       "hipMemcpyAsync(tables)");

@@ -5,57 +5,105 @@
 namespace sapq {
 
 // ================================================================ layout conversion
-template <int P>
-__global__ void k_pack_spinor(GeomDev g, typename Prec<P>::S2 *dst, const double2 *src, double scale) {
+// the value a store rounds v to (the storage precision), as a later load would read it
+__device__ __forceinline__ cx<double> as_stored(const double2 *, cx<double> v) { return v; }
+__device__ __forceinline__ cx<float> as_stored(const float2 *, cx<float> v) { return v; }
+__device__ __forceinline__ cx<float> as_stored(const __half2 *, cx<float> v) {
+    const float2 f = __half22float2(__floats2half2_rn(v.r, v.i));
+    return {f.x, f.y};
+}
+__device__ __forceinline__ cx<float> as_stored(const __hip_bfloat162 *, cx<float> v) {
+    return {__bfloat162float(__float2bfloat16(v.r)), __bfloat162float(__float2bfloat16(v.i))};
+}
+
+// A spinor field between the interchange layout (records of 12 complex per site, in
+// lexicographic site order) and the internal one ([block][12][slot]).  Bound by memory: both
+// sides are read or written once.  A record is contiguous on one side and a run of slots on
+// the other, so LAY_SITES sites go through an LDS tile: consecutive threads move consecutive
+// components of a record on the interchange side and consecutive slots on the internal side.
+// (One thread per site, with the other side strided by 192 bytes, took 100 us in and 137 us out
+// for a 24^3x48 FP64 field of 2 x 127 MB; this takes about 47 us each, 5.4 TB/s.)  The tile's pitch of 13 components leaves both
+// directions free of bank conflicts for 4-, 8- and 16-byte components.  Records share 128-byte
+// lines with their x neighbours, which lie in the same block: XCD-contiguous workgroups find
+// those lines in their L2.
+constexpr int LAY_SITES = 128, LAY_THREADS = 256, LAY_PITCH = 13;
+
+// the workgroup's sites: lexicographic index of each into lex[], this thread's internal slot
+// (site threadIdx.x % LAY_SITES) as an offset of component 0; -1 past the last site
+template <typename G>
+__device__ __forceinline__ long lay_sites(const G &g, int *lex, long &i0) {
+    static_assert(LAY_THREADS % LAY_SITES == 0, "a thread keeps its slot");
+    i0 = xcd_site_base(LAY_SITES);
+    const long i = i0 + threadIdx.x % LAY_SITES;
+    if (i >= g.V) return -1;
+    const unsigned ib = (unsigned)i / (unsigned)g.Vb, s = (unsigned)i - ib * (unsigned)g.Vb;
+    if (threadIdx.x < LAY_SITES) lex[threadIdx.x] = g.blk_off[ib] + g.slot_off[s];
+    return (long)ib * 12 * g.Vb + s;
+}
+
+// T2: type of the interchange side, double2 or float2
+template <int P, typename T2>
+__global__ void __launch_bounds__(LAY_THREADS) k_pack_spinor(GeomDev g, typename Prec<P>::S2 *__restrict__ dst,
+                                                            const T2 *__restrict__ src, double scale) {
     using C = typename Prec<P>::C;
-    long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= g.V) return;
-    int ib = (int)(i / g.Vb), s = (int)(i - (long)ib * g.Vb);
-    const double2 *p = src + lex_site(g, ib, s) * 12;
-    typename Prec<P>::S2 *q = dst + (size_t)ib * 12 * g.Vb + s;
+    using S2 = typename Prec<P>::S2;
+    __shared__ S2 tile[LAY_SITES * LAY_PITCH];
+    __shared__ int lex[LAY_SITES];
+    long i0;
+    const long slot = lay_sites(g, lex, i0);
+    __syncthreads();
+    constexpr int N = LAY_SITES * 12 / LAY_THREADS;
 #pragma unroll
-    for (int c = 0; c < 12; ++c) {
-        double2 v = p[c];
-        st(q + (size_t)c * g.Vb, cx<C>{C(v.x * scale), C(v.y * scale)});
+    for (int k = 0; k < N; ++k) {
+        const int e = threadIdx.x + k * LAY_THREADS, t = e / 12, c = e % 12;
+        if (i0 + t < g.V) {
+            const T2 v = src[(size_t)lex[t] * 12 + c];
+            st(&tile[t * LAY_PITCH + c], cx<C>{C(v.x * scale), C(v.y * scale)});
+        }
     }
+    __syncthreads();
+    if (slot < 0) return;
+    const int t = threadIdx.x % LAY_SITES;
+#pragma unroll
+    for (int c = threadIdx.x / LAY_SITES; c < 12; c += LAY_THREADS / LAY_SITES)
+        dst[slot + (size_t)c * g.Vb] = tile[t * LAY_PITCH + c];
 }
 
-// FP32 (re, im) pairs in the interchange layout -> FP32 internal layout
-__global__ void k_pack_spinor_f32(GeomDev g, float2 *dst, const float2 *src) {
-    long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= g.V) return;
-    int ib = (int)(i / g.Vb), s = (int)(i - (long)ib * g.Vb);
-    const float2 *p = src + lex_site(g, ib, s) * 12;
-    float2 *q = dst + (size_t)ib * 12 * g.Vb + s;
+// SUB: src - src2, rounded to the storage precision, instead of src
+template <int P, typename T2, bool SUB>
+__global__ void __launch_bounds__(LAY_THREADS) k_unpack_spinor(GeomDev g, T2 *__restrict__ dst,
+                                                              const typename Prec<P>::S2 *__restrict__ src,
+                                                              const typename Prec<P>::S2 *__restrict__ src2,
+                                                              double scale) {
+    using S2 = typename Prec<P>::S2;
+    using T = decltype(T2::x);
+    __shared__ S2 tile[LAY_SITES * LAY_PITCH];
+    __shared__ int lex[LAY_SITES];
+    long i0;
+    const long slot = lay_sites(g, lex, i0);
+    if (slot >= 0) {
+        const int t = threadIdx.x % LAY_SITES;
 #pragma unroll
-    for (int c = 0; c < 12; ++c) q[(size_t)c * g.Vb] = p[c];
-}
-
-// FP64 internal layout -> FP32 (re, im) pairs in the interchange layout (rounded)
-__global__ void k_unpack_spinor_f32(GeomDev g, float2 *dst, const double2 *src) {
-    long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= g.V) return;
-    int ib = (int)(i / g.Vb), s = (int)(i - (long)ib * g.Vb);
-    float2 *p = dst + lex_site(g, ib, s) * 12;
-    const double2 *q = src + (size_t)ib * 12 * g.Vb + s;
-#pragma unroll
-    for (int c = 0; c < 12; ++c) {
-        const double2 v = q[(size_t)c * g.Vb];
-        p[c] = make_float2((float)v.x, (float)v.y);
+        for (int k = 0; k < 12 * LAY_SITES / LAY_THREADS; ++k) {
+            const int c = threadIdx.x / LAY_SITES + k * (LAY_THREADS / LAY_SITES);
+            const size_t o = slot + (size_t)c * g.Vb;
+            if constexpr (SUB)
+                st(&tile[t * LAY_PITCH + c], ld(src + o) - ld(src2 + o));
+            else
+                tile[t * LAY_PITCH + c] = src[o];
+        }
     }
-}
-
-template <int P>
-__global__ void k_unpack_spinor(GeomDev g, double2 *dst, const typename Prec<P>::S2 *src, double scale) {
-    long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= g.V) return;
-    int ib = (int)(i / g.Vb), s = (int)(i - (long)ib * g.Vb);
-    double2 *p = dst + lex_site(g, ib, s) * 12;
-    const typename Prec<P>::S2 *q = src + (size_t)ib * 12 * g.Vb + s;
+    __syncthreads();
 #pragma unroll
-    for (int c = 0; c < 12; ++c) {
-        auto v = ld(q + (size_t)c * g.Vb);
-        p[c] = make_double2((double)v.r * scale, (double)v.i * scale);
+    for (int k = 0; k < 12 * LAY_SITES / LAY_THREADS; ++k) {
+        const int e = threadIdx.x + k * LAY_THREADS, t = e / 12, c = e % 12;
+        if (i0 + t < g.V) {
+            const auto v = ld(&tile[t * LAY_PITCH + c]);
+            T2 o;
+            o.x = T((double)v.r * scale);
+            o.y = T((double)v.i * scale);
+            dst[(size_t)lex[t] * 12 + c] = o;
+        }
     }
 }
 
@@ -480,17 +528,6 @@ __global__ void __launch_bounds__(RED_THREADS) k_dots(size_t n, int nd, const ty
     }
 }
 
-// the value a store rounds v to (the storage precision), as a later load would read it
-__device__ __forceinline__ cx<double> as_stored(const double2 *, cx<double> v) { return v; }
-__device__ __forceinline__ cx<float> as_stored(const float2 *, cx<float> v) { return v; }
-__device__ __forceinline__ cx<float> as_stored(const __half2 *, cx<float> v) {
-    const float2 f = __half22float2(__floats2half2_rn(v.r, v.i));
-    return {f.x, f.y};
-}
-__device__ __forceinline__ cx<float> as_stored(const __hip_bfloat162 *, cx<float> v) {
-    return {__bfloat162float(__float2bfloat16(v.r)), __bfloat162float(__float2bfloat16(v.i))};
-}
-
 // z = x + a y, and in the same pass the partial sums per workgroup, in double, of <w, z> (w
 // not null), <z, z> (zz) and <z, x> (zx), taken on z as stored: the Krylov update and the inner
 // products that follow it read the vectors once
@@ -601,22 +638,37 @@ __global__ void k_zero(size_t n, typename Prec<P>::S2 *d) {
 static inline unsigned grid_for(long n, int t) { return (unsigned)((n + t - 1) / t); }
 static constexpr unsigned BLAS_GRID = 1024;
 
+static inline unsigned lay_grid(const Ctx *c) { return (grid_for(c->V, LAY_SITES) + N_XCD - 1) / N_XCD * N_XCD; }
+
 void launch_pack_spinor(Ctx *c, int prec, void *dst, const double *src, double scale) {
-    PREC_SWITCH(prec, (k_pack_spinor<P_><<<grid_for(c->V, 256), 256, 0, c->stream>>>(
+    PREC_SWITCH(prec, (k_pack_spinor<P_, double2><<<lay_grid(c), LAY_THREADS, 0, c->stream>>>(
                           c->g, (typename Prec<P_>::S2 *)dst, (const double2 *)src, scale)));
 }
 
+// FP32 (re, im) pairs in the interchange layout -> FP32 internal layout
 void launch_pack_spinor_f32(Ctx *c, void *dst, const float *src) {
-    k_pack_spinor_f32<<<grid_for(c->V, 256), 256, 0, c->stream>>>(c->g, (float2 *)dst, (const float2 *)src);
+    k_pack_spinor<SAPQ_FP32, float2><<<lay_grid(c), LAY_THREADS, 0, c->stream>>>(c->g, (float2 *)dst, (const float2 *)src, 1.0);
 }
 
+// FP64 internal layout -> FP32 (re, im) pairs in the interchange layout (rounded)
 void launch_unpack_spinor_f32(Ctx *c, float *dst, const double2 *src) {
-    k_unpack_spinor_f32<<<grid_for(c->V, 256), 256, 0, c->stream>>>(c->g, (float2 *)dst, src);
+    k_unpack_spinor<SAPQ_FP64, float2, false><<<lay_grid(c), LAY_THREADS, 0, c->stream>>>(c->g, (float2 *)dst, src, src, 1.0);
 }
 
 void launch_unpack_spinor(Ctx *c, int prec, double *dst, const void *src, double scale) {
-    PREC_SWITCH(prec, (k_unpack_spinor<P_><<<grid_for(c->V, 256), 256, 0, c->stream>>>(
-                          c->g, (double2 *)dst, (const typename Prec<P_>::S2 *)src, scale)));
+    PREC_SWITCH(prec, ({
+                    using S2 = typename Prec<P_>::S2;
+                    k_unpack_spinor<P_, double2, false><<<lay_grid(c), LAY_THREADS, 0, c->stream>>>(
+                        c->g, (double2 *)dst, (const S2 *)src, (const S2 *)src, scale);
+                }));
+}
+
+void launch_unpack_diff(Ctx *c, int prec, double *dst, const void *a, const void *b) {
+    INNER_SWITCH(prec, ({
+                     using S2 = typename Prec<P_>::S2;
+                     k_unpack_spinor<P_, double2, true><<<lay_grid(c), LAY_THREADS, 0, c->stream>>>(
+                         c->g, (double2 *)dst, (const S2 *)a, (const S2 *)b, 1.0);
+                 }));
 }
 
 int launch_pack_links(Ctx *c, const double *U, double *max_dev) {

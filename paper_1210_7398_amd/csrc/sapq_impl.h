@@ -40,12 +40,10 @@ struct GeomDev {
     const unsigned *nbr16;  // [4][Vb]: forward | backward << 16 slots of direction mu, bit 15/31 = inside
     const int *blk_nbr;     // [8][NB]: neighbouring block id | WRAP_BIT
     const int *plane_start; // [nplanes + 1]
-    const int *slot_lex;    // [Vb] block-local lexicographic index of each slot
-    const int *blk_lex;     // [NB] lexicographic block index of each internal block id
+    const int *slot_off;    // [Vb] lexicographic site index of each slot, counted from its block's origin
+    const int *blk_off;     // [NB] lexicographic site index of each block's origin
     const int *lex_blk;     // [NB] internal block id of each lexicographic block index
     const int *zord_blk;    // [NB] internal block ids in Z (Morton) order of the block coordinates
-    int B[4];
-    int nbk[4];             // blocks per direction
 };
 
 // ---------------------------------------------------------------- storage precisions
@@ -177,6 +175,8 @@ struct Ctx;
 // kernel launchers (defined in the .hip files)
 void launch_pack_spinor(Ctx *c, int prec, void *dst, const double *src, double scale);
 void launch_unpack_spinor(Ctx *c, int prec, double *dst, const void *src, double scale);
+// dst = a - b in the inner storage precision prec
+void launch_unpack_diff(Ctx *c, int prec, double *dst, const void *a, const void *b);
 int launch_pack_links(Ctx *c, const double *U, double *max_dev);
 void launch_pack_clover(Ctx *c, const double *F);
 bool launch_permute_fields(Ctx *c, const int *perm);

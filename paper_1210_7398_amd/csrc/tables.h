@@ -21,6 +21,7 @@ struct HostTables {
     int Vb = 0, NB = 0, nplanes = 0, max_plane = 0;
     int nbk[4];
     std::vector<int> loc_nbr, blk_nbr, plane_start, slot_lex, blk_lex, lex_blk, zord_blk;
+    std::vector<int> slot_off, blk_off;  // lexicographic site index = blk_off[ib] + slot_off[s]
     std::vector<int> nbr16;  // packed forward/backward slots per direction (stored as unsigned)
 };
 
@@ -76,6 +77,13 @@ inline void build_tables(const sapq_geom *G, HostTables &T) {
     for (int p = 0; p < H; ++p) T.plane_start[p + 1] += T.plane_start[p];
     T.max_plane = 0;
     for (int p = 0; p < H; ++p) T.max_plane = std::max(T.max_plane, T.plane_start[p + 1] - T.plane_start[p]);
+    const int *L = G->L;
+    T.slot_off.resize(Vb);
+    for (int s = 0; s < Vb; ++s) {
+        int r = T.slot_lex[s], n = 0, stride = 1;
+        for (int m = 0; m < 4; ++m) { n += r % B[m] * stride; r /= B[m]; stride *= L[m]; }
+        T.slot_off[s] = n;
+    }
     // in-block neighbours
     T.loc_nbr.resize(8 * Vb);
     for (int s = 0; s < Vb; ++s) {
@@ -110,6 +118,12 @@ inline void build_tables(const sapq_geom *G, HostTables &T) {
             for (int m = 0; m < 4; ++m) { sum += r % T.nbk[m]; r /= T.nbk[m]; }
             if ((sum & 1) == col) T.blk_lex.push_back(b);
         }
+    T.blk_off.resize(NB);
+    for (int i = 0; i < NB; ++i) {
+        int r = T.blk_lex[i], n = 0, stride = 1;
+        for (int m = 0; m < 4; ++m) { n += r % T.nbk[m] * B[m] * stride; r /= T.nbk[m]; stride *= L[m]; }
+        T.blk_off[i] = n;
+    }
     std::vector<int> ib_of(NB);
     for (int i = 0; i < NB; ++i) ib_of[T.blk_lex[i]] = i;
     T.lex_blk = ib_of;
