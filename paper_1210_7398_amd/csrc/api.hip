@@ -139,6 +139,7 @@ static void carve(Ctx *c, Arena &A, const HostTables &T, const PartTables &PT) {
         c->nn_alloc = true;
         float **w[] = {&c->nn_w, &c->nn_wq, &c->nn_G, &c->nn_m, &c->nn_v};
         for (auto p : w) *p = (float *)A.take(NN_PARAMS * sizeof(float));
+        c->nn_part = (float *)A.take(nn_wgrad_elems(V) * sizeof(float));
         c->nn_wt = (float2 *)A.take(9 * NN_C * NN_C * 16 * sizeof(float2));
         struct { float2 **p; int ch; } f[] = {{&c->nn_a0, 1}, {&c->nn_a1, NN_C}, {&c->nn_a2, NN_C}, {&c->nn_z, 1},
                                                {&c->nn_gz, 1}, {&c->nn_g2, NN_C}, {&c->nn_g1, NN_C}, {&c->nn_gin, 1},

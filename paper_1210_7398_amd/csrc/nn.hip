@@ -14,6 +14,8 @@
 // per 16-byte piece: piece k of channel c (components 2k, 2k + 1 in FP32, 4k .. 4k + 3 in
 // BF16) sits at piece index (K i + k) NN_C + c (K = 6 or 3), so the 8 channel threads of a
 // site read 128 contiguous bytes per load instruction.
+#include <algorithm>
+
 #include "sitecore.h"
 
 namespace sapq {
@@ -187,7 +189,7 @@ __device__ __forceinline__ void nn_transport1(cx<float> t[12], const S2 *__restr
     }
 }
 
-// ---------------------------------------------------------------- FP32 layer, weight gradient
+// ---------------------------------------------------------------- FP32 layer
 // out[c'] for one output channel c' = blockIdx.y; weights W[9][COUT][CIN][16] complex (float2)
 template <int CIN, int COUT>
 __global__ void __launch_bounds__(256) k_nn_layer(GeomDev g, const float2 *__restrict__ in, float2 *__restrict__ out,
@@ -222,49 +224,219 @@ __global__ void __launch_bounds__(256) k_nn_layer(GeomDev g, const float2 *__res
     store_chan<REC_F32>(out, COUT, g, ib, s, co, acc);
 }
 
-// G[d][c'][c] (16 complex) = sum_n sum_a gout[c'](n)[al][a] conj((T_d in[c])(n)[be][a]), added to G.
-// One workgroup per (d, c', c); a fixed-order tree finishes the sum.
-template <int RT>
-__global__ void __launch_bounds__(256) k_nn_wgrad(GeomDev g, int cin, int cout, const float2 *__restrict__ gout,
-                                                 const float2 *__restrict__ in, const float2 *__restrict__ L,
-                                                 float2 *__restrict__ G) {
-    __shared__ float sm[32][257];
-    const int d = blockIdx.x, co = blockIdx.y, ci = blockIdx.z;
-    float acc[32];
+// ---------------------------------------------------------------- weight gradient
+// G[d][c'][c][al][be] += sum_n sum_a gout[c'](n)[al][a] conj((T_d in[c])(n)[be][a]): a real product
+// with rows (al, re/im, c'), columns (be, re/im, c) and the reduction over (site, colour).  Its
+// operands are FP32 (the transports are), so it runs on the FP32 matrix cores
+// (v_mfma_f32_16x16x4f32, 157 TFLOP/s), which also removes the repeated work: every transport is
+// made once instead of once per output channel.  A workgroup takes a contiguous chunk of sites
+// in tiles staged in LDS and writes its partial products; k_nn_wgrad_sum adds the chunks in a
+// fixed order.  A tile's products start from zero and are added to the running sums, so that
+// no FP32 chain is longer than a tile or the number of tiles (relative error of the
+// gradient against 64 bits at 16^3x32, FP32 records: 4.4e-7; one chain over a chunk gave 1.3e-6,
+// one thread's chain over V / 256 sites 5.9e-7).
+// At 16^3x32 sites the three layers take 555 us (8 x 8 channels 361, 80 TFLOP/s on the 29 GFLOP
+// it cannot do without; the thin layers 80 each), against 9630 us with one workgroup per
+// (d, c', c) and vector arithmetic.
+constexpr int WG_SPLITS = 85;
+
+int nn_wgrad_splits(long V) { return (int)std::min<long>(WG_SPLITS, (V + 127) / 128); }
+// partial products: 9 x splits of 64 x 64 (8 x 8 channels) or 8 x splits of 72 x 64 (one thin side)
+size_t nn_wgrad_elems(long V) { return (size_t)9 * nn_wgrad_splits(V) * 64 * NN_C * NN_C; }
+
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+// LDS rows (spin, re/im, channel) of an operand, channels fastest, so that the 8 threads of a
+// site write to different banks.  The pitch, 4 mod 8 floats, makes a wave's 16-byte fragment
+// reads (16 rows x 4 groups) hit every bank once.
+template <int C> __device__ __forceinline__ int wg_row(int sp, int ri, int c) { return (2 * sp + ri) * C + c; }
+
+template <int C, int PITCH>
+__device__ __forceinline__ void wg_put(float (*T)[PITCH], int t, int c, const cx<float> v[12]) {
 #pragma unroll
-    for (int k = 0; k < 32; ++k) acc[k] = 0.f;
-    for (long i = threadIdx.x; i < g.V; i += blockDim.x) {
-        const int ib = (int)(i / g.Vb), s = (int)(i - (long)ib * g.Vb);
-        int nb, ns;
-        float ph;
-        nn_neighbour(g, ib, s, d, nb, ns, ph);
-        cx<float> t[12], go[12];
-        nn_transport<RT>(t, in, cin, g, L, ib, s, d, ci, nb, ns);
-        load_chan<RT>(go, gout, cout, g, ib, s, co);
+    for (int sp = 0; sp < 4; ++sp)
 #pragma unroll
-        for (int al = 0; al < 4; ++al)
+        for (int a = 0; a < 3; ++a) {
+            T[wg_row<C>(sp, 0, c)][3 * t + a] = v[3 * sp + a].r;
+            T[wg_row<C>(sp, 1, c)][3 * t + a] = v[3 * sp + a].i;
+        }
+}
+
+// acc[i][j] += A rows [16 (ra + i), +16) times B rows [16 (rb + j), +16), over K columns.  The
+// reduction index runs in any order, the same for both operands: lane l takes
+// 16 kk + 4 (l / 16) + q in product q.
+template <int TA, int TB, int K, int PITCH>
+__device__ __forceinline__ void wg_tile(f32x4 (&acc)[TA][TB], const float (*A)[PITCH], const float (*B)[PITCH], int ra,
+                                        int rb, int lane) {
+    f32x4 p[TA][TB];
 #pragma unroll
-            for (int be = 0; be < 4; ++be) {
-                cx<float> v = cxz<float>();
+    for (int i = 0; i < TA; ++i)
 #pragma unroll
-                for (int a = 0; a < 3; ++a) v = v + cmulc(t[3 * be + a], go[3 * al + a]);
-                acc[2 * (4 * al + be)] += v.r;
-                acc[2 * (4 * al + be) + 1] += v.i;
+        for (int j = 0; j < TB; ++j) p[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int kk = 0; kk < K / 16; ++kk) {
+        f32x4 fa[TA], fb[TB];
+#pragma unroll
+        for (int i = 0; i < TA; ++i)
+            fa[i] = *reinterpret_cast<const f32x4 *>(&A[(ra + i) * 16 + (lane & 15)][kk * 16 + 4 * (lane >> 4)]);
+#pragma unroll
+        for (int j = 0; j < TB; ++j)
+            fb[j] = *reinterpret_cast<const f32x4 *>(&B[(rb + j) * 16 + (lane & 15)][kk * 16 + 4 * (lane >> 4)]);
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+#pragma unroll
+            for (int i = 0; i < TA; ++i)
+#pragma unroll
+                for (int j = 0; j < TB; ++j)
+                    p[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(fa[i][q], fb[j][q], p[i][j], 0, 0, 0);
+    }
+#pragma unroll
+    for (int i = 0; i < TA; ++i)
+#pragma unroll
+        for (int j = 0; j < TB; ++j) acc[i][j] += p[i][j];
+}
+
+// partial products to part[row][col] of 64 columns; lane l of a product holds rows
+// 4 (l / 16) + q of column l % 16
+template <int TA, int TB>
+__device__ __forceinline__ void wg_store(float *o, const f32x4 (&acc)[TA][TB], int ra, int rb, int lane, int rows) {
+#pragma unroll
+    for (int i = 0; i < TA; ++i)
+#pragma unroll
+        for (int j = 0; j < TB; ++j)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int row = (ra + i) * 16 + 4 * (lane >> 4) + q;
+                if (row < rows) o[row * 64 + (rb + j) * 16 + (lane & 15)] = acc[i][j][q];
             }
-    }
+}
+
+__device__ __forceinline__ void wg_site(const GeomDev &g, long i, int &ib, int &s) {
+    ib = (int)((unsigned)i / (unsigned)g.Vb);
+    s = (int)(i - (long)ib * g.Vb);
+}
+
+// Eight channels on both sides: one d per workgroup, tiles of 32 sites, one (site, channel) per
+// thread on each side, 2 x 2 products per wave.  51 KB of LDS, three workgroups a CU, whose
+// transports and products overlap; 9 x 85 workgroups are one round of them.
+template <int RT>
+__global__ void __launch_bounds__(256) k_nn_wgrad8(GeomDev g, const float2 *__restrict__ gout,
+                                                  const float2 *__restrict__ in, const float2 *__restrict__ L,
+                                                  float *__restrict__ part, int tiles_per_split) {
+    constexpr int NS = 32, K = 3 * NS, PITCH = K + 4;
+    __shared__ __attribute__((aligned(16))) float As[64][PITCH], Bs[64][PITCH];
+    const int d = blockIdx.x, split = blockIdx.y;
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, ra = 2 * (wave >> 1), rb = 2 * (wave & 1);
+    f32x4 acc[2][2];
 #pragma unroll
-    for (int k = 0; k < 32; ++k) sm[k][threadIdx.x] = acc[k];
-    __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w)
+    for (int i = 0; i < 4; ++i) acc[i >> 1][i & 1] = f32x4{0.f, 0.f, 0.f, 0.f};
+    const long n0 = (long)split * tiles_per_split * NS, n1 = min((long)g.V, n0 + (long)tiles_per_split * NS);
+    const int c = threadIdx.x % NN_C, t = threadIdx.x / NN_C;
+    for (long s0 = n0; s0 < n1; s0 += NS) {
+        cx<float> T[12], go[12];
+        if (s0 + t < n1) {
+            int ib, s, nb, ns;
+            float ph;
+            wg_site(g, s0 + t, ib, s);
+            nn_neighbour(g, ib, s, d, nb, ns, ph);
+            nn_transport<RT>(T, in, NN_C, g, L, ib, s, d, c, nb, ns);
+            load_rec<RT>(go, gout, s0 + t, NN_C, c);
+        } else {
 #pragma unroll
-            for (int k = 0; k < 32; ++k) sm[k][threadIdx.x] += sm[k][threadIdx.x + w];
+            for (int e = 0; e < 12; ++e) T[e] = go[e] = cxz<float>();
+        }
+        __syncthreads();  // the last tile has been read
+        wg_put<NN_C>(As, t, c, go);
+        wg_put<NN_C>(Bs, t, c, T);
         __syncthreads();
+        wg_tile<2, 2, K>(acc, As, Bs, ra, rb, lane);
     }
-    if (threadIdx.x < 16) {
-        float2 *p = G + (((size_t)d * cout + co) * cin + ci) * 16 + threadIdx.x;
-        float2 o = *p;
-        *p = make_float2(o.x + sm[2 * threadIdx.x][0], o.y + sm[2 * threadIdx.x + 1][0]);
+    wg_store(part + ((size_t)d * gridDim.y + split) * 4096, acc, ra, rb, lane, 64);
+}
+
+// One channel on one side (the thin one: the input of the first layer, the output gradient of
+// the last) and eight on the other.  All nine transports are taken of the thin side, so the wide
+// side is read once and not transported: sum_n gout(n) conj((T_d in)(n)) is also
+// sum_m (T_rev(d) gout)(m) conj(in(m)), T_rev(d) being the inverse of the unitary T_d.  Rows
+// (transport, spin, re/im) of the thin side, 72 padded to 80; tiles of 16 sites, whose 144
+// transports and 128 wide records are shared out over the 256 threads; wave w multiplies all five
+// row tiles by column tile w.
+constexpr int WG_THIN = 8;  // chunks per chunk of the 8 x 8 layer
+
+template <int RT>
+__global__ void __launch_bounds__(256) k_nn_wgrad1(GeomDev g, const float2 *__restrict__ thin,
+                                                  const float2 *__restrict__ wide, const float2 *__restrict__ L,
+                                                  float *__restrict__ part, int tiles_per_split) {
+    constexpr int NS = 16, K = 3 * NS, PITCH = K + 4;
+    __shared__ __attribute__((aligned(16))) float As[80][PITCH], Bs[64][PITCH];
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    for (int w = threadIdx.x; w < 8 * PITCH; w += 256) As[72 + w / PITCH][w % PITCH] = 0.f;
+    f32x4 acc[5][1];
+#pragma unroll
+    for (int i = 0; i < 5; ++i) acc[i][0] = f32x4{0.f, 0.f, 0.f, 0.f};
+    const long n0 = (long)blockIdx.x * tiles_per_split * NS, n1 = min((long)g.V, n0 + (long)tiles_per_split * NS);
+    const int tt = threadIdx.x % NS, td = threadIdx.x / NS;                     // transport
+    const int wc = threadIdx.x % NN_C, wt = (255 - (int)threadIdx.x) / NN_C;    // wide record
+    for (long s0 = n0; s0 < n1; s0 += NS) {
+        cx<float> T[12], W[12];
+#pragma unroll
+        for (int e = 0; e < 12; ++e) T[e] = W[e] = cxz<float>();
+        if (td < 9 && s0 + tt < n1) {
+            int ib, s, nb, ns;
+            float ph;
+            wg_site(g, s0 + tt, ib, s);
+            nn_neighbour(g, ib, s, td, nb, ns, ph);
+            nn_transport1(T, thin, g, L, ib, s, td, nb, ns);
+        }
+        if (wt < NS && s0 + wt < n1) load_rec<RT>(W, wide, s0 + wt, NN_C, wc);
+        __syncthreads();  // the last tile has been read
+        if (td < 9) wg_put<1>(&As[8 * td], tt, 0, T);
+        if (wt < NS) wg_put<NN_C>(Bs, wt, wc, W);
+        __syncthreads();
+        wg_tile<5, 1, K>(acc, As, Bs, 0, wave, lane);
+    }
+    wg_store(part + (size_t)blockIdx.x * (72 * 64), acc, 0, wave, lane, 72);
+}
+
+// G += the complex entries of the summed partial products: 256 / PARTS entries per workgroup, each
+// entry's chunks shared by PARTS threads and added in a fixed order, in double
+template <int CIN, int COUT, int PARTS>
+__global__ void __launch_bounds__(256) k_nn_wgrad_sum(int splits, const float *__restrict__ part, float2 *__restrict__ G) {
+    constexpr int E = 256 / PARTS;
+    __shared__ double sm[2][PARTS][E];
+    const int e = threadIdx.x % E, p = threadIdx.x / E;
+    int o = blockIdx.x * E + e;
+    const int ci = o % CIN; o /= CIN;
+    const int be = o % 4; o /= 4;
+    const int al = o % 4; o /= 4;
+    const int co = o % COUT, d = o / COUT;
+    // element (row of gout, column of in) of a chunk's products, for the re / im of each
+    auto at = [&](int ro, int ri) {
+        if constexpr (CIN == NN_C && COUT == NN_C) return wg_row<COUT>(al, ro, co) * 64 + wg_row<CIN>(be, ri, ci);
+        if constexpr (CIN == 1) return (8 * d + wg_row<1>(be, ri, 0)) * 64 + wg_row<NN_C>(al, ro, co);
+        const int rd = d == 0 ? 0 : ((d & 1) ? d + 1 : d - 1);
+        return (8 * rd + wg_row<1>(al, ro, 0)) * 64 + wg_row<NN_C>(be, ri, ci);
+    };
+    const int rr = at(0, 0), ii = at(1, 1), ir = at(1, 0), rim = at(0, 1);
+    constexpr bool wide = CIN == NN_C && COUT == NN_C;
+    const size_t stride = wide ? 4096 : 72 * 64;
+    const float *q = part + (wide ? (size_t)d * splits * stride : 0);
+    double re = 0, im = 0;
+    for (int k = p; k < splits; k += PARTS) {
+        re += (double)q[k * stride + rr] + (double)q[k * stride + ii];
+        im += (double)q[k * stride + ir] - (double)q[k * stride + rim];
+    }
+    sm[0][p][e] = re;
+    sm[1][p][e] = im;
+    __syncthreads();
+    if (threadIdx.x < E) {
+        re = im = 0;
+        for (int k = 0; k < PARTS; ++k) {
+            re += sm[0][k][e];
+            im += sm[1][k][e];
+        }
+        float2 *w = G + (((size_t)d * COUT + co) * CIN + ci) * 16 + 4 * al + be;
+        *w = make_float2(w->x + (float)re, w->y + (float)im);
     }
 }
 
@@ -646,11 +818,29 @@ void launch_nn_layer(Ctx *c, int cin, int cout, const float2 *in, float2 *out, c
 }
 
 void launch_nn_wgrad(Ctx *c, int cin, int cout, const float2 *gout, const float2 *in, float2 *G, bool bf16_records) {
-    dim3 grid(9, (unsigned)cout, (unsigned)cin);
+    int splits = nn_wgrad_splits(c->V);
+    float *part = c->nn_part;
+    if (cin == NN_C && cout == NN_C) {
+        const int per = (int)((c->V + 31) / 32 + splits - 1) / splits;
+        const dim3 grid(9, (unsigned)splits);
+        if (bf16_records)
+            k_nn_wgrad8<REC_BF16><<<grid, 256, 0, c->stream>>>(c->g, gout, in, c->nn_L, part, per);
+        else
+            k_nn_wgrad8<REC_F32><<<grid, 256, 0, c->stream>>>(c->g, gout, in, c->nn_L, part, per);
+        k_nn_wgrad_sum<NN_C, NN_C, 16><<<9 * NN_C * NN_C, 256, 0, c->stream>>>(splits, part, G);
+        return;
+    }
+    splits *= WG_THIN;
+    const int per = (int)((c->V + 15) / 16 + splits - 1) / splits;
+    const float2 *thin = cin == 1 ? in : gout, *wide = cin == 1 ? gout : in;
     if (bf16_records)
-        k_nn_wgrad<REC_BF16><<<grid, 256, 0, c->stream>>>(c->g, cin, cout, gout, in, c->nn_L, G);
+        k_nn_wgrad1<REC_BF16><<<splits, 256, 0, c->stream>>>(c->g, thin, wide, c->nn_L, part, per);
     else
-        k_nn_wgrad<REC_F32><<<grid, 256, 0, c->stream>>>(c->g, cin, cout, gout, in, c->nn_L, G);
+        k_nn_wgrad1<REC_F32><<<splits, 256, 0, c->stream>>>(c->g, thin, wide, c->nn_L, part, per);
+    if (cin == 1)
+        k_nn_wgrad_sum<1, NN_C, 64><<<9 * NN_C * 4, 256, 0, c->stream>>>(splits, part, G);
+    else
+        k_nn_wgrad_sum<NN_C, 1, 64><<<9 * NN_C * 4, 256, 0, c->stream>>>(splits, part, G);
 }
 
 void launch_nn_adjoint_weights(Ctx *c, int cin, int cout, const float2 *W, float2 *Wt) {

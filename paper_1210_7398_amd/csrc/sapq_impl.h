@@ -285,6 +285,7 @@ struct Ctx {
     // learned stage (allocated when params.flags & SAPQ_FLAG_NN)
     bool nn_alloc = false, have_nn = false;
     float *nn_w, *nn_wq, *nn_G, *nn_m, *nn_v;
+    float *nn_part;                      // partial products of a weight gradient
     float2 *nn_wt;                       // adjoint weights of one layer
     float2 *nn_a0, *nn_a1, *nn_a2, *nn_z; // layer inputs (1, 8, 8 channels) and output
     float2 *nn_gz, *nn_g2, *nn_g1, *nn_gin, *nn_e;
@@ -307,6 +308,7 @@ void launch_nn_adam(Ctx *c, int n, float *w, const float *grad, float gscale, fl
 void launch_nn_round(Ctx *c, int n, const float *w, float *wq);
 size_t nn_afrag_elems(int cin, int cout);
 size_t nn_link_elems(const Ctx *c);
+size_t nn_wgrad_elems(long V);  // floats of partial products a weight gradient needs
 void launch_nn_links(Ctx *c);
 void launch_nn_afrag(Ctx *c, int cin, int cout, const float2 *W, void *A);
 // p_in / p_out: storage precision of a one-channel input / output (spinor layout); skip:
