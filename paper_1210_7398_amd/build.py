@@ -12,7 +12,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OUT = os.path.join(HERE, "libsapq.so")
 OBJ = os.path.join(HERE, "_build")
-SOURCES = ["api.hip", "kernels.hip", "sap_parts.hip", "sap_eomr.hip", "nn.hip", "batch.hip", "noalloc.hip"]
+SOURCES = ["api.hip", "kernels.hip", "sap_parts.hip", "sap_eomr.hip", "sap_eo.hip", "nn.hip", "batch.hip", "noalloc.hip"]
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950",

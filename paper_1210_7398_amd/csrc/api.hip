@@ -132,6 +132,8 @@ static void carve(Ctx *c, Arena &A, const HostTables &T, const PartTables &PT) {
         c->part_imps = ints(PT.imp_start.size());
         c->part_nb = (uint2 *)A.take(PT.pnb.size() * sizeof(unsigned));
         c->part_gnb = (uint2 *)A.take(PT.gnb.size() * sizeof(unsigned));
+        c->eo_nb = (uint4 *)A.take((size_t)T.Vb * sizeof(uint4));
+        c->eo_face = (unsigned *)ints((size_t)8 * T.Vb);
         c->xch = (unsigned long long *)A.take((size_t)(T.NB / 2) * PT.NP * 3 * 24 * std::max(PT.Hp, 1) * 8);
         c->xsync = (unsigned *)A.take(4 * sizeof(unsigned));
     }
@@ -175,7 +177,9 @@ static int check_params(const sapq_params *p, std::string &why) {
     return SAPQ_OK;
 }
 
-static int upload_parts(Ctx *c, const PartTables &PT) {
+static int upload_parts(Ctx *c, const HostTables &T, const PartTables &PT) {
+    EoHostTables E;
+    build_eo(T, E);
     struct { void *dst; const void *src; size_t bytes; } cp[] = {
         {c->part_gslot, PT.gslot.data(), PT.gslot.size() * sizeof(int)},
         {c->part_pstart, PT.pstart.data(), PT.pstart.size() * sizeof(int)},
@@ -183,12 +187,14 @@ static int upload_parts(Ctx *c, const PartTables &PT) {
         {c->part_imp, PT.imp.data(), PT.imp.size() * sizeof(int)},
         {c->part_imps, PT.imp_start.data(), PT.imp_start.size() * sizeof(int)},
         {c->part_nb, PT.pnb.data(), PT.pnb.size() * sizeof(unsigned)},
-        {c->part_gnb, PT.gnb.data(), PT.gnb.size() * sizeof(unsigned)}};
+        {c->part_gnb, PT.gnb.data(), PT.gnb.size() * sizeof(unsigned)},
+        {c->eo_nb, E.nb.data(), E.nb.size() * sizeof(unsigned)},
+        {c->eo_face, E.face.data(), E.face.size() * sizeof(unsigned)}};
     for (auto &e : cp) {
         int rc = hipcheck(hipMemcpyAsync(e.dst, e.src, e.bytes, hipMemcpyHostToDevice, c->stream), "hipMemcpyAsync(part tables)");
         if (rc) return rc;
     }
-    return SAPQ_OK;
+    return hipcheck(hipStreamSynchronize(c->stream), "hipStreamSynchronize");  // E lives until here
 }
 
 // The two workgroups of a block wait on each other with a bounded spin; a time-out (or a
@@ -357,7 +363,7 @@ int sapq_create(const sapq_geom *geom, const sapq_params *params, void *arena, s
         if (rc) { hipHostFree(c->host_res); delete h; return rc; }
     }
     if (c->use_parts) {
-        rc = upload_parts(c, PT);
+        rc = upload_parts(c, T, PT);
         if (rc == SAPQ_OK)
             rc = hipcheck(hipMemsetAsync(c->xch, 0, (size_t)c->g.NBc * PT.NP * 3 * 24 * std::max(PT.Hp, 1) * 8, c->stream),
                           "hipMemsetAsync(halo)");
@@ -366,10 +372,10 @@ int sapq_create(const sapq_geom *geom, const sapq_params *params, void *arena, s
     }
     rc = hipcheck(hipStreamSynchronize(c->stream), "hipStreamSynchronize");
     if (rc) { hipHostFree(c->host_res); delete h; return rc; }
-    bool lds_ok = !(set_sap_lds_limits(c) || set_parts_lds_limit(c) || set_eomr_lds_limit(c));
+    bool lds_ok = !(set_sap_lds_limits(c) || set_parts_lds_limit(c) || set_eomr_lds_limit(c) || set_eo_lds_limit(c));
     if (lds_ok && c->fb_fp32) {  // the FP32 instantiations the fallback would launch
         c->prm.prec_inner = SAPQ_FP32;
-        lds_ok = !(set_sap_lds_limits(c) || set_parts_lds_limit(c) || set_eomr_lds_limit(c));
+        lds_ok = !(set_sap_lds_limits(c) || set_parts_lds_limit(c) || set_eomr_lds_limit(c) || set_eo_lds_limit(c));
         c->prm.prec_inner = c->prec_created;
     }
     if (!lds_ok) {
@@ -514,11 +520,12 @@ int sapq_ssor(sapq_ctx *h, double *x, const double *v, int colour) {
 static void msap(Ctx *c, const void *v, void *y) {
     for (int j = 0; j < c->prm.n_sap; ++j) {
         const void *src = j == 0 ? v : c->sap_r;
+        const bool last = j == c->prm.n_sap - 1;
         int t = prof_begin(c, SAPQ_K_PHASE_E);
-        launch_sap_phase(c, 0, j == 0, src, c->sap_r, c->sap_x, y);
+        launch_sap_phase(c, 0, j == 0, last, src, c->sap_r, c->sap_x, y);
         prof_end(c, t);
         t = prof_begin(c, SAPQ_K_PHASE_O);
-        launch_sap_phase(c, 1, j == 0, src, c->sap_r, c->sap_x, y);
+        launch_sap_phase(c, 1, j == 0, last, src, c->sap_r, c->sap_x, y);
         prof_end(c, t);
     }
     int t = prof_begin(c, SAPQ_K_FACE);
@@ -586,8 +593,8 @@ int sapq_dk(sapq_ctx *h, double *x, double *w, const double *v) {
     if (rc) return rc;
     int pi = c->prm.prec_inner;
     launch_pack_spinor(c, pi, c->i_tmp, v, 1.0);
-    launch_sap_phase(c, 0, true, c->i_tmp, c->sap_r, c->sap_x, c->i_ph);
-    launch_sap_phase(c, 1, true, c->i_tmp, c->sap_r, c->sap_x, c->i_ph);
+    launch_sap_phase(c, 0, true, true, c->i_tmp, c->sap_r, c->sap_x, c->i_ph);
+    launch_sap_phase(c, 1, true, true, c->i_tmp, c->sap_r, c->sap_x, c->i_ph);
     launch_sap_face(c, 0, c->sap_r, c->sap_x);
     launch_unpack_spinor(c, pi, x, c->sap_x, 1.0);
     launch_unpack_diff(c, pi, w, c->i_tmp, c->sap_r);  // w = v - r
@@ -1085,7 +1092,7 @@ static int apply_subblock(Ctx *c, const int S[4]) {
             set_error("sub-block shape does not fit the split of the block");
             return SAPQ_ESHAPE;
         }
-        rc = upload_parts(c, PT);
+        rc = upload_parts(c, T, PT);
         if (rc) return rc;
     } else if (T.nplanes > MAX_PLANES || T.max_plane * 4 > 512) {
         set_error("sub-block shape gives too large a hyperplane");

@@ -15,6 +15,7 @@
 #include <string>
 #include <vector>
 
+#include "sapeo.h"
 #include "twolane.h"
 
 namespace sapq {
@@ -42,6 +43,7 @@ struct BField {
     const uint2 *pnb, *gnb;
     const int *pst;
     int tpr;
+    EoTables eo;  // one-lane even-odd kernel
 };
 
 struct BatchDev {
@@ -351,6 +353,34 @@ __global__ void __launch_bounds__(768) k_bsap_phase_2l(const BatchDev *__restric
         for (int e = 0; e < 6; ++e) v[e] = v[e] - xv[e] + kappa * out[e];
         store6(r, ib, i, d, Vb, v);
     }
+}
+
+// The one-lane even-odd phase (csrc/sapeo.h) of one source per workgroup, over the same work
+// list.
+template <int P, int NS>
+__global__ void __attribute__((amdgpu_waves_per_eu(2))) __launch_bounds__(EO_THREADS)
+k_bsap_phase_eo(const BatchDev *__restrict__ Bd, int colour, int mode, int s_src, int s_r, int s_x, int s_y,
+                const BState *__restrict__ bst) {
+    using S2 = typename Prec<P>::S2;
+    extern __shared__ float4 xb[];
+    const BatchDev &B = *Bd;
+    if ((int)blockIdx.x >= B.work0[B.nf]) return;
+    int fi, k;
+    const int ib = work_item(B, blockIdx.x, colour, fi, k);
+    if (ib < 0) return;
+    const BField &F = B.f[fi];
+    if (bst[F.rhs0 + k].done) return;
+    const size_t ko = (size_t)k * F.nvec;
+    eo_phase<P, NS>(F.g, F.eo, xb, ib, mode, F.n_ssor, F.kappa, (const S2 *)F.iv[s_src] + ko, (S2 *)F.iv[s_r] + ko,
+                    (S2 *)F.iv[s_x] + ko, (S2 *)F.iv[s_y] + ko, (const S2 *)F.Uin, (const S2 *)F.Fin);
+}
+
+template <int P> static void *beo_kernel(int cls) {
+    return cls == 0 ? (void *)k_bsap_phase_eo<P, EO_NS[0]> : cls == 1 ? (void *)k_bsap_phase_eo<P, EO_NS[1]>
+                                                                      : (void *)k_bsap_phase_eo<P, EO_NS[2]>;
+}
+static void *beo_kernel(int prec, int Vb) {
+    return prec == SAPQ_FP16 ? beo_kernel<SAPQ_FP16>(eo_class(Vb)) : beo_kernel<SAPQ_BF16>(eo_class(Vb));
 }
 
 // allow the batched phase kernels the dynamic LDS they are launched with
@@ -818,6 +848,7 @@ struct Batch {
     long max_V = 0;
     int prec = SAPQ_FP32, NR = 1;
     bool two_lane = false;  // k_bsap_phase_2l (else the four-lane k_bsap_phase)
+    bool eo = false;        // k_bsap_phase_eo: every context runs the one-lane even-odd kernel, one source per workgroup
     bool use_nn = false;    // every context has the learned stage on
     int threads = 0;
     size_t lds = 0;
@@ -920,6 +951,14 @@ static int setup_batch(Batch &B, sapq_ctx *const *ctxs, int nctx, const int *nrh
     if (B.NR == 0) { why = "the SAP block is too large for the batched kernel's LDS"; return SAPQ_ESHAPE; }
     B.lds = per * B.NR + extra;
     B.threads = B.two_lane ? B.NR * tpr : c0->ssor_threads;
+    B.eo = B.NR == 1;
+    for (Ctx *c : B.ctx) B.eo = B.eo && eo_supported(c);
+    if (B.eo) {
+        B.threads = eo_tables(c0).T;
+        B.lds = eo_lds_bytes(c0->g.Vb, B.threads);
+        if (B.lds > 65536)
+            (void)hipFuncSetAttribute(beo_kernel(B.prec, c0->g.Vb), hipFuncAttributeMaxDynamicSharedMemorySize, (int)B.lds);
+    }
     if (B.lds > 65536) {
         batch_lds_attr((int)B.lds);
         (void)hipGetLastError();  // clears the runtime's last-error slot
@@ -946,6 +985,7 @@ static int setup_batch(Batch &B, sapq_ctx *const *ctxs, int nctx, const int *nrh
         F.gnb = c->part_gnb;
         F.pst = c->part_pstart;
         F.tpr = c->part_threads;
+        if (B.eo) F.eo = eo_tables(c);
         B.host.work0[f] = work;
         work += (c->g.NBc + N_XCD - 1) / N_XCD * N_XCD * F.ngroups;  // a multiple of 8 (work_item)
         B.total += nrhs[f];
@@ -979,6 +1019,15 @@ static void bmsap(Batch &B, int src, int y) {
     for (int j = 0; j < c0->prm.n_sap; ++j) {
         const int s = j == 0 ? src : IV_SAPR;
         for (int colour = 0; colour < 2; ++colour) {
+            if (B.eo) {
+                int mode = (colour == 1 || j > 0 ? EO_GATHER : 0) | (j == 0 ? EO_FIRST : EO_R_ZERO) |
+                           (j == c0->prm.n_sap - 1 ? EO_LAST : 0);
+                int src_ = s, r_ = IV_SAPR, x_ = IV_SAPX;
+                void *args[] = {&B.dev, &colour, &mode, &src_, &r_, &x_, &y, &B.st};
+                (void)hipLaunchKernel(beo_kernel(B.prec, c0->g.Vb), dim3((unsigned)B.host.work0[B.nf]), dim3(B.threads), args,
+                                      B.lds, B.stream);
+                continue;
+            }
             BPREC(B.prec, ({
                       if (B.NR == 4) bphase<P_, 4>(B, colour, j == 0, s, IV_SAPR, IV_SAPX, y);
                       else if (B.NR == 3) bphase<P_, 3>(B, colour, j == 0, s, IV_SAPR, IV_SAPX, y);

@@ -805,9 +805,13 @@ int set_sap_lds_limits(Ctx *c) {
     return hipGetLastError() == hipSuccess ? 0 : -1;  // also clears the runtime's last-error slot
 }
 
-void launch_sap_phase(Ctx *c, int colour, bool first, const void *rsrc, void *r, void *x, void *y) {
+void launch_sap_phase(Ctx *c, int colour, bool first, bool last, const void *rsrc, void *r, void *x, void *y) {
     if (c->prm.flags & SAPQ_FLAG_EOMR) {
         launch_sap_phase_eomr(c, colour, (colour == 1 || !first) ? 1 : 0, first ? 1 : 0, 0, rsrc, r, x, y);
+        return;
+    }
+    if (eo_supported(c)) {
+        launch_sap_phase_eo(c, colour, colour == 1 || !first, first, last, false, rsrc, r, x, y);
         return;
     }
     if (c->use_parts) {
@@ -828,6 +832,10 @@ void launch_sap_phase(Ctx *c, int colour, bool first, const void *rsrc, void *r,
 void launch_ssor_only(Ctx *c, int colour, const void *v, void *x) {
     if (c->prm.flags & SAPQ_FLAG_EOMR) {
         launch_sap_phase_eomr(c, colour, 0, 1, 1, v, nullptr, x, nullptr);
+        return;
+    }
+    if (eo_supported(c)) {
+        launch_sap_phase_eo(c, colour, false, true, true, true, v, nullptr, x, nullptr);
         return;
     }
     if (c->use_parts) {

@@ -181,11 +181,17 @@ int launch_pack_links(Ctx *c, const double *U, double *max_dev);
 void launch_pack_clover(Ctx *c, const double *F);
 bool launch_permute_fields(Ctx *c, const int *perm);
 void launch_dslash(Ctx *c, int prec, void *out, const void *in);
-void launch_sap_phase(Ctx *c, int colour, bool first, const void *rsrc, void *r, void *x, void *y);
+// first / last: the phase belongs to the first / last of the M_SAP cycles (first: rsrc is not r)
+void launch_sap_phase(Ctx *c, int colour, bool first, bool last, const void *rsrc, void *r, void *x, void *y);
 void launch_sap_face(Ctx *c, int colour, void *r, const void *x);
 void launch_sap_phase_parts(Ctx *c, int colour, int gather, int first, int ssor_only, const void *rsrc, void *r,
                             void *x, void *y);
 int set_parts_lds_limit(Ctx *c);
+// the one-lane phase kernel of the even-odd site order, where it applies
+bool eo_supported(const Ctx *c);
+void launch_sap_phase_eo(Ctx *c, int colour, bool gather, bool first, bool last, bool ssor_only, const void *rsrc, void *r,
+                         void *x, void *y);
+int set_eo_lds_limit(Ctx *c);
 // the even-odd minimal-residual block solve (SAPQ_FLAG_EOMR) in place of the SSOR
 bool eomr_supported(const Ctx *c, std::string &why);
 void launch_sap_phase_eomr(Ctx *c, int colour, int gather, int first, int ssor_only, const void *rsrc, void *r,
@@ -247,6 +253,8 @@ struct Ctx {
     bool parts_staged = false;  // phase kernel in the staged load order (one workgroup per CU by LDS)
     int *part_gslot, *part_pstart, *part_exp, *part_imp, *part_imps;
     uint2 *part_nb, *part_gnb;
+    uint4 *eo_nb;  // tables of the one-lane even-odd phase kernel (csrc/sapeo.h)
+    unsigned *eo_face;
     unsigned long long *xch;  // tagged halo words exchanged between the two workgroups of a block
     unsigned *xsync;          // ticket, done, epoch, error
     long V;

@@ -288,6 +288,30 @@ inline bool build_parts(const sapq_geom *G, const HostTables &T, int NP, PartTab
     return true;
 }
 
+// Tables of the one-lane even-odd phase kernel: per slot the LDS slots of the eight in-block
+// neighbours +x -x +y -y ... (two per word; Vb, the zero slot, for one outside the block), and per
+// direction the Vb / B[mu] sites of its forward face and then those of its backward one, each
+// as slot | slot of the neighbour in the next block << 16.
+struct EoHostTables {
+    std::vector<unsigned> nb;    // [Vb][4]
+    std::vector<unsigned> face;  // [4][2 Vb]: room for a direction of one site, whose faces are the block
+};
+
+inline void build_eo(const HostTables &T, EoHostTables &E) {
+    const int Vb = T.Vb;
+    E.nb.assign((size_t)4 * Vb, 0);
+    E.face.assign((size_t)8 * Vb, 0);
+    int n = 0;
+    for (int k = 0; k < 8; ++k) {
+        if (k % 2 == 0) n = 0;
+        for (int s = 0; s < Vb; ++s) {
+            const int t = T.loc_nbr[(size_t)k * Vb + s];
+            E.nb[(size_t)4 * s + k / 2] |= (unsigned)(t >= 0 ? t : Vb) << (16 * (k % 2));
+            if (t < 0) E.face[(size_t)(k / 2) * 2 * Vb + n++] = (unsigned)s | (unsigned)(-1 - t) << 16;
+        }
+    }
+}
+
 // Sync words of the split phase kernel ([0] ticket, [1] done, [2] epoch, [3] error) to use
 // after a launch that raised the error word.  The halo words that launch left in the
 // exchange array carry its epoch (or an earlier one), so the epoch only moves forward: the
