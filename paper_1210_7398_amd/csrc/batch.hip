@@ -256,9 +256,9 @@ __global__ void __launch_bounds__(768) k_bsap_phase_2l(const BatchDev *__restric
     const int tpr = F.tpr;
     const int k = threadIdx.x / tpr, tt = threadIdx.x - k * tpr;
     const int d = tt & 1, q0 = tt >> 1, nq = tpr >> 1;
-    const int Vb = g.Vb, NS = Vb + 1;
+    const int Vb = g.Vb;
     const bool live = k < NR && k0 + k < F.nrhs;
-    float4 *xs = xb + (size_t)min(k, NR - 1) * 6 * NS;
+    float4 *xs = xb + (size_t)min(k, NR - 1) * 6 * (Vb + 1);
     const size_t ko = (size_t)(k0 + min(k, NR - 1)) * F.nvec;
     const S2 *U = (const S2 *)F.Uin;
     const S2 *Fk = (const S2 *)F.Fin + ((size_t)ib * 2 + d) * 18 * Vb;
@@ -295,9 +295,9 @@ __global__ void __launch_bounds__(768) k_bsap_phase_2l(const BatchDev *__restric
             }
             store6(r, ib, i, d, Vb, v);
 #pragma unroll
-            for (int q = 0; q < 3; ++q) xs[(3 * d + q) * NS + i] = make_float4(0.f, 0.f, 0.f, 0.f);
+            for (int q = 0; q < 3; ++q) xs[6 * i + 3 * d + q] = make_float4(0.f, 0.f, 0.f, 0.f);
         }
-        for (int t = tt; t < 6; t += tpr) xs[t * NS + Vb] = make_float4(0.f, 0.f, 0.f, 0.f);
+        for (int t = tt; t < 6; t += tpr) xs[6 * Vb + t] = make_float4(0.f, 0.f, 0.f, 0.f);
     }
     __syncthreads();
 
@@ -311,11 +311,11 @@ __global__ void __launch_bounds__(768) k_bsap_phase_2l(const BatchDev *__restric
             const int h = (sw & 1) == 0 ? pi : H - 1 - pi;
             for (int i = F.pst[h] + q0; live && i < F.pst[h + 1]; i += nq) {
                 cx<float> out[6], v[6];
-                block_hop_clover(out, xs, NS, F.pnb[2 * i + d], F.gnb[i], U, Fk, ib, i, d, Vb, sg);
+                block_hop_clover(out, xs, F.pnb[2 * i + d], F.gnb[i], U, Fk, ib, i, d, Vb, sg);
                 load6(v, r, ib, i, d, Vb);
 #pragma unroll
                 for (int q = 0; q < 3; ++q) {
-                    float4 *o = &xs[(3 * d + q) * NS + i];
+                    float4 *o = &xs[6 * i + 3 * d + q];
                     const float4 ov = *o;
                     const cx<float> n0 = v[2 * q] + kappa * out[2 * q], n1 = v[2 * q + 1] + kappa * out[2 * q + 1];
                     *o = make_float4((1.f - omega) * ov.x + omega * n0.r, (1.f - omega) * ov.y + omega * n0.i,
@@ -330,12 +330,7 @@ __global__ void __launch_bounds__(768) k_bsap_phase_2l(const BatchDev *__restric
     if (!live) return;
     for (int i = q0; i < Vb; i += nq) {
         cx<float> xv[6], yv[6];
-#pragma unroll
-        for (int q = 0; q < 3; ++q) {
-            const float4 f = xs[(3 * d + q) * NS + i];
-            xv[2 * q] = {f.x, f.y};
-            xv[2 * q + 1] = {f.z, f.w};
-        }
+        lds_get6(xv, xs, d, i);
         store6(x, ib, i, d, Vb, xv);
         if (first) {
 #pragma unroll
@@ -347,7 +342,7 @@ __global__ void __launch_bounds__(768) k_bsap_phase_2l(const BatchDev *__restric
         }
         store6(y, ib, i, d, Vb, yv);
         cx<float> out[6], v[6];
-        block_hop_clover(out, xs, NS, F.pnb[2 * i + d], F.gnb[i], U, Fk, ib, i, d, Vb, sg);
+        block_hop_clover(out, xs, F.pnb[2 * i + d], F.gnb[i], U, Fk, ib, i, d, Vb, sg);
         load6(v, r, ib, i, d, Vb);
 #pragma unroll
         for (int e = 0; e < 6; ++e) v[e] = v[e] - xv[e] + kappa * out[e];

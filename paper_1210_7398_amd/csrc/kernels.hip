@@ -197,8 +197,6 @@ __global__ void __launch_bounds__(2 * dslash_sites(P)) k_dslash(GeomDev g, typen
     const int ib = g.lex_blk[bl];
     const C sg = d ? C(-1) : C(1);
     cx<C> acc[12];
-#pragma unroll
-    for (int c = 0; c < 12; ++c) acc[c] = cxz<C>();
     hop_any<0>(acc, g, in, U, ib, s, d, sg);
     hop_any<1>(acc, g, in, U, ib, s, d, sg);
     hop_any<2>(acc, g, in, U, ib, s, d, sg);

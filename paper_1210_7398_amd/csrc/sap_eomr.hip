@@ -56,19 +56,6 @@ __device__ __forceinline__ void block_sum3(double &a, double &b, double &c, doub
     }
 }
 
-__device__ __forceinline__ void lds_put6(float4 *xs, int NS, int d, int i, const cx<float> v[6]) {
-#pragma unroll
-    for (int q = 0; q < 3; ++q) xs[(3 * d + q) * NS + i] = make_float4(v[2 * q].r, v[2 * q].i, v[2 * q + 1].r, v[2 * q + 1].i);
-}
-__device__ __forceinline__ void lds_get6(cx<float> v[6], const float4 *xs, int NS, int d, int i) {
-#pragma unroll
-    for (int q = 0; q < 3; ++q) {
-        const float4 f = xs[(3 * d + q) * NS + i];
-        v[2 * q] = {f.x, f.y};
-        v[2 * q + 1] = {f.z, f.w};
-    }
-}
-
 // K: sites of one parity per lane pair, the smallest that covers the block (x_e and p of
 // those sites stay in registers across the steps)
 template <int P, int K>
@@ -80,7 +67,7 @@ __global__ void __launch_bounds__(512) k_sap_phase_eomr(GeomDev g, EomrArgs a, c
     using S2 = typename Prec<P>::S2;
     extern __shared__ float4 xs[];
     __shared__ double red[3 * EOMR_WAVES];
-    const int Vb = g.Vb, NS = Vb + 1, Ve = a.pstart[1];
+    const int Vb = g.Vb, Ve = a.pstart[1];
     const int ib = a.colour * g.NBc + blockIdx.x;
     const int d = threadIdx.x & 1;
     const int q0 = threadIdx.x >> 1, nq = blockDim.x >> 1;
@@ -120,9 +107,9 @@ __global__ void __launch_bounds__(512) k_sap_phase_eomr(GeomDev g, EomrArgs a, c
             if (i < Ve)
 #pragma unroll
                 for (int e = 0; e < 6; ++e) v[e] = cxz<float>();
-            lds_put6(xs, NS, d, i, v);
+            lds_put6(xs, d, i, v);
         }
-        if (threadIdx.x < 6) xs[threadIdx.x * NS + Vb] = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (threadIdx.x < 6) xs[6 * Vb + threadIdx.x] = make_float4(0.f, 0.f, 0.f, 0.f);
     }
     __syncthreads();
 
@@ -136,11 +123,11 @@ __global__ void __launch_bounds__(512) k_sap_phase_eomr(GeomDev g, EomrArgs a, c
         for (int e = 0; e < 6; ++e) xe[k][e] = cxz<float>();
         if (i < Ve) {
             cx<float> out[6], v[6];
-            block_hop_clover_seq(out, xs, NS, a.pnb[2 * i + d], a.gnb[i], U, Fk, ib, i, d, Vb, sg);
+            block_hop_clover_seq(out, xs, a.pnb[2 * i + d], a.gnb[i], U, Fk, ib, i, d, Vb, sg);
             load6(v, vb, ib, i, d, Vb);
 #pragma unroll
             for (int e = 0; e < 6; ++e) v[e] = v[e] + kappa * out[e];
-            lds_put6(xs, NS, d, i, v);
+            lds_put6(xs, d, i, v);
         }
     }
     __syncthreads();
@@ -150,10 +137,10 @@ __global__ void __launch_bounds__(512) k_sap_phase_eomr(GeomDev g, EomrArgs a, c
         // (a) t_o = K_oe r_e onto the odd slots
         for (int i = Ve + q0; i < Vb; i += nq) {
             cx<float> out[6];
-            block_hop_clover_seq(out, xs, NS, a.pnb[2 * i + d], a.gnb[i], U, Fk, ib, i, d, Vb, sg);
+            block_hop_clover_seq(out, xs, a.pnb[2 * i + d], a.gnb[i], U, Fk, ib, i, d, Vb, sg);
 #pragma unroll
             for (int e = 0; e < 6; ++e) out[e] = kappa * out[e];
-            lds_put6(xs, NS, d, i, out);
+            lds_put6(xs, d, i, out);
         }
         __syncthreads();
         // (b) p = r_e - K_eo t_o and the partial sums of <p, r> and <p, p>
@@ -166,8 +153,8 @@ __global__ void __launch_bounds__(512) k_sap_phase_eomr(GeomDev g, EomrArgs a, c
             for (int e = 0; e < 6; ++e) pe[k][e] = cxz<float>();
             if (i < Ve) {
                 cx<float> out[6], rv[6];
-                block_hop_clover_seq(out, xs, NS, a.pnb[2 * i + d], a.gnb[i], U, Fk, ib, i, d, Vb, sg);
-                lds_get6(rv, xs, NS, d, i);
+                block_hop_clover_seq(out, xs, a.pnb[2 * i + d], a.gnb[i], U, Fk, ib, i, d, Vb, sg);
+                lds_get6(rv, xs, d, i);
 #pragma unroll
                 for (int e = 0; e < 6; ++e) {
                     pe[k][e] = rv[e] - kappa * out[e];
@@ -186,13 +173,13 @@ __global__ void __launch_bounds__(512) k_sap_phase_eomr(GeomDev g, EomrArgs a, c
             const int i = q0 + k * nq;
             if (i < Ve) {
                 cx<float> rv[6];
-                lds_get6(rv, xs, NS, d, i);
+                lds_get6(rv, xs, d, i);
 #pragma unroll
                 for (int e = 0; e < 6; ++e) {
                     xe[k][e] = {xe[k][e].r + ar * rv[e].r - ai * rv[e].i, xe[k][e].i + ar * rv[e].i + ai * rv[e].r};
                     rv[e] = {rv[e].r - (ar * pe[k][e].r - ai * pe[k][e].i), rv[e].i - (ar * pe[k][e].i + ai * pe[k][e].r)};
                 }
-                lds_put6(xs, NS, d, i, rv);
+                lds_put6(xs, d, i, rv);
             }
         }
         __syncthreads();
@@ -202,23 +189,23 @@ __global__ void __launch_bounds__(512) k_sap_phase_eomr(GeomDev g, EomrArgs a, c
 #pragma unroll
     for (int k = 0; k < K; ++k) {
         const int i = q0 + k * nq;
-        if (i < Ve) lds_put6(xs, NS, d, i, xe[k]);
+        if (i < Ve) lds_put6(xs, d, i, xe[k]);
     }
     __syncthreads();
     for (int i = Ve + q0; i < Vb; i += nq) {
         cx<float> out[6], v[6];
-        block_hop_clover_seq(out, xs, NS, a.pnb[2 * i + d], a.gnb[i], U, Fk, ib, i, d, Vb, sg);
+        block_hop_clover_seq(out, xs, a.pnb[2 * i + d], a.gnb[i], U, Fk, ib, i, d, Vb, sg);
         load6(v, vb, ib, i, d, Vb);
 #pragma unroll
         for (int e = 0; e < 6; ++e) v[e] = v[e] + kappa * out[e];
-        lds_put6(xs, NS, d, i, v);
+        lds_put6(xs, d, i, v);
     }
     __syncthreads();
 
     // 5. outputs: x_c, y_c += x_c, r_c = v_c - A_cc x_c
     for (int i = q0; i < Vb; i += nq) {
         cx<float> xv[6];
-        lds_get6(xv, xs, NS, d, i);
+        lds_get6(xv, xs, d, i);
         store6(x, ib, i, d, Vb, xv);
         if (a.ssor_only) continue;
         cx<float> yv[6];
@@ -232,7 +219,7 @@ __global__ void __launch_bounds__(512) k_sap_phase_eomr(GeomDev g, EomrArgs a, c
         }
         store6(y, ib, i, d, Vb, yv);
         cx<float> out[6], v[6];
-        block_hop_clover_seq(out, xs, NS, a.pnb[2 * i + d], a.gnb[i], U, Fk, ib, i, d, Vb, sg);
+        block_hop_clover_seq(out, xs, a.pnb[2 * i + d], a.gnb[i], U, Fk, ib, i, d, Vb, sg);
         load6(v, r, ib, i, d, Vb);
 #pragma unroll
         for (int e = 0; e < 6; ++e) v[e] = v[e] - xv[e] + kappa * out[e];

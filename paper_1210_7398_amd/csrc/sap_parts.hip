@@ -24,6 +24,21 @@
 // moved on (writing sweep w + 3 needs the reader's sweep w + 2 data).  The two parts of a
 // block take their block from a ticket counter in start order, so a part only ever waits
 // on a part that is already running; the last workgroup resets the counter.
+//
+// What bounds it: the dependent chain of a hyperplane step (table entries, loads, LDS reads, about
+// 760 vector instructions of a site update per lane, LDS store, barrier), with one or two waves
+// a SIMD.  Cycle stamps of the 24^3x48 launch showed 2700 of a step's 13000 cycles outside the
+// update: every wave copied a share of the halo words (with integer divisions by their number),
+// read the hyperplane starts from LDS, and a pointer choice between LDS and global memory made
+// flat loads, after which every wait is for all loads in flight.  With a wave of its own for the
+// halo words, the starts in registers (v_readlane), record-wise LDS, the dagger of the backward
+// links folded into signs the instructions take anyway (902 -> 760) and no relaxation
+// arithmetic at omega = 1, a launch takes 458 us instead of 533 (FP32, 6^3x12 blocks, the same
+// bits).  Measured and not kept: a site's links, or all it needs, loaded a step ahead (507 us with
+// two hops' links, 10% slower than without once the waits were exact; all of it spills in FP32
+// and gains nothing in FP16).
+#include <algorithm>
+
 #include "twolane.h"
 
 namespace sapq {
@@ -31,7 +46,8 @@ namespace sapq {
 struct PartArgs {
     int colour, gather, first, ssor_only, n_ssor;
     float kappa, omega;
-    int NP, Vp, Hp;
+    int Vp, Hp;
+    int sweep_waves, halo_wave;  // waves that update sites; the wave that copies halo words
     const int *gslot;         // [NP][Vp] block slot of each part-local site
     const uint2 *pnb;         // [NP][Vp][2] LDS slots of the 4 neighbours of lane d (16 bits each)
     const uint2 *gnb;         // [NP][Vp] block slots of the 4 backward neighbours (16 bits each)
@@ -46,7 +62,6 @@ struct PartArgs {
                               // written word then carries the awaited tag)
 };
 
-constexpr int IMP_REGS = 4;          // halo words a thread keeps in flight during a step
 constexpr int SPIN_LIMIT = 1 << 20;  // default bounded wait on a halo word (about a second)
 
 __device__ __forceinline__ unsigned xch_tag(unsigned epoch, int sweep) {
@@ -84,8 +99,8 @@ __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(
 // STAGED: the load order of a site update (block_hop_clover_impl); the staged order holds
 // about 40 more registers, which costs nothing where a workgroup's LDS already keeps the CU
 // to one workgroup, and occupancy where several workgroups share a CU
-template <int P, bool STAGED>
-__global__ void __launch_bounds__(512) k_sap_phase_parts(GeomDev g, PartArgs a, const typename Prec<P>::S2 *rsrc,
+template <int P, int NP, bool STAGED>
+__global__ void __launch_bounds__(512, STAGED ? 2 : 3) k_sap_phase_parts(GeomDev g, PartArgs a, const typename Prec<P>::S2 *rsrc,
                                                          typename Prec<P>::S2 *r, typename Prec<P>::S2 *x,
                                                          typename Prec<P>::S2 *y,
                                                          const typename Prec<P>::S2 *__restrict__ U,
@@ -93,10 +108,10 @@ __global__ void __launch_bounds__(512) k_sap_phase_parts(GeomDev g, PartArgs a, 
     using S2 = typename Prec<P>::S2;
     extern __shared__ float4 xs[];
     __shared__ unsigned sh_ticket;
-    const int Vb = g.Vb, Vp = a.Vp, Hp = a.Hp, NS = Vp + Hp + 1;
+    const int Vb = g.Vb, Vp = a.Vp, Hp = a.Hp;
     int blk = blockIdx.x, part = 0;
     unsigned epoch = 0;
-    if (a.NP == 2) {
+    if (NP == 2) {
         if (threadIdx.x == 0) sh_ticket = atomicAdd(&a.sync[0], 1u);
         __syncthreads();
         const unsigned t = sh_ticket;
@@ -118,10 +133,9 @@ __global__ void __launch_bounds__(512) k_sap_phase_parts(GeomDev g, PartArgs a, 
     const int *expi = a.exp_idx + (size_t)part * Vp;
     const int *imp = a.imp + (size_t)part * Hp;
     const int *imps = a.imp_start + (size_t)part * (MAX_PLANES + 1);
-    int *xsi = reinterpret_cast<int *>(xs);
     const size_t xstride = (size_t)3 * 24 * Hp;
-    unsigned long long *xo = a.xch + ((size_t)blk * a.NP + part) * xstride;
-    unsigned long long *xi = a.xch + ((size_t)blk * a.NP + (part ^ 1)) * xstride;
+    unsigned long long *xo = a.xch + ((size_t)blk * NP + part) * xstride;
+    unsigned long long *xi = a.xch + ((size_t)blk * NP + (part ^ 1)) * xstride;
     const uint2 *gnb = a.gnb + (size_t)part * Vp;
     const S2 *Fk = F + ((size_t)ib * 2 + d) * 18 * Vb;
     const S2 *vb = a.ssor_only ? rsrc : r;
@@ -157,147 +171,120 @@ __global__ void __launch_bounds__(512) k_sap_phase_parts(GeomDev g, PartArgs a, 
                 store6(r, ib, s, d, Vb, v);
             }
 #pragma unroll
-            for (int q = 0; q < 3; ++q) xs[(3 * d + q) * NS + i] = make_float4(0.f, 0.f, 0.f, 0.f);
+            for (int q = 0; q < 3; ++q) xs[6 * i + 3 * d + q] = make_float4(0.f, 0.f, 0.f, 0.f);
         }
-        for (int t = threadIdx.x; t < 6 * (Hp + 1); t += blockDim.x)
-            xs[(t / (Hp + 1)) * NS + Vp + t % (Hp + 1)] = make_float4(0.f, 0.f, 0.f, 0.f);
-        // the hyperplane and halo-import starts into LDS behind the iterate: every step reads
-        // them, and from global memory (which the kernel writes, so they cannot go through the
-        // scalar cache) each read would be a load round trip at the head of the step
-        for (int t = threadIdx.x; t < MAX_PLANES + 1; t += blockDim.x) {
-            xsi[6 * 4 * NS + t] = a.pstart[t];
-            xsi[6 * 4 * NS + MAX_PLANES + 1 + t] = imps[t];
-        }
+        for (int t = threadIdx.x; t < 6 * (Hp + 1); t += blockDim.x) xs[6 * Vp + t] = make_float4(0.f, 0.f, 0.f, 0.f);
     }
     __syncthreads();
 
     // 2. sweeps: x_n <- (1 - omega) x_n + omega (v_n + kappa F(n) sum_{m in block} H_nm x_m)
     const int H = g.nplanes, nsw = 2 * a.n_ssor;
-    const int *pst = xsi + 6 * 4 * NS;  // the hyperplane starts, copied to LDS in step 1
-    imps = pst + MAX_PLANES + 1;         // and this part's halo-import starts
+    // The hyperplane and halo-import starts, lane l holding entries l and l + 1: a step reads them
+    // with v_readlane, where LDS or global reads would put a round trip at the head of every step.
+    const int lane = threadIdx.x & 63;
+    const int pl0 = a.pstart[lane], pl1 = a.pstart[lane + 1];
+    const int im0 = imps[lane], im1 = imps[lane + 1];
+    auto at = [](int v, int h) { return __builtin_amdgcn_readlane(v, h); };
+    // the boundary words of a site, tagged with the sweep
+    auto publish = [&](const cx<float> xn[6], int kx, int w) {
+        if (kx < 0) return;
+        const unsigned wt = xch_tag(epoch, w);
+        unsigned long long *dst = xo + ((w % 3) * 24 + 12 * d) * Hp + kx;
+#pragma unroll
+        for (int e = 0; e < 6; ++e) {
+            xch_put(dst + (2 * e) * Hp, xn[e].r, wt);
+            xch_put(dst + (2 * e + 1) * Hp, xn[e].i, wt);
+        }
+    };
     // The table entries of a site (LDS slots of its neighbours, block slots of its backward
     // neighbours, boundary index) are read one step ahead, for this thread's first site of
-    // the coming hyperplane, right after its current update: read at the start of their own
-    // step they would put a load round trip ahead of every other load of the step.
+    // the coming hyperplane: read at the start of their own step they would put a load round
+    // trip ahead of every other load of the step.
     uint2 nb_n = make_uint2(0u, 0u), gl_n = make_uint2(0u, 0u);
     int kx_n = -1;
-    auto tables_for = [&](int hh) {
-        const int i = pst[hh] + q0;
-        if (i < pst[hh + 1]) {
+    auto tables_for = [&](int h) {
+        const int i = at(pl0, h) + q0;
+        if (i < at(pl1, h)) {
             nb_n = pnb[2 * i + d];
             gl_n = gnb[i];
-            kx_n = a.NP == 2 ? expi[i] : -1;
+            kx_n = NP == 2 ? expi[i] : -1;
         }
     };
     tables_for(0);
+    const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), nwv = blockDim.x >> 6;
+    // The halo words of `n` slots (slot index k(e)) from sweep slot `src`, checked against `tag`, into
+    // LDS, one slot per lane: all 24 loads in flight, then the waits.
+    auto import_words = [&](int n, auto k_of, int src, unsigned tag) {
+        for (int e = lane; e < n; e += 64) {
+            const int k = k_of(e);
+            unsigned long long *p = xi + (src + k), word[24];
+#pragma unroll
+            for (int c = 0; c < 24; ++c) word[c] = xch_get(p + c * Hp);
+#pragma unroll
+            for (int c = 0; c < 24; ++c) xsf[24 * (Vp + k) + c] = xch_wait(word[c], p + c * Hp, tag, gave_up, a);
+        }
+    };
     for (int w = 0; w < nsw; ++w) {
         const bool fwd = (w & 1) == 0;
         for (int pi = 0; pi < H; ++pi) {
-            const int h = fwd ? pi : H - 1 - pi;
-            // (1) halo words for the next step, stored to LDS after this step's updates.  At
-            // the turn of a sweep the plane repeats and its halo slots already hold the right
-            // sweep (or the plane reads none), so nothing is fetched.
-            int nw = 0, ne = 0, e0 = 0;
-            unsigned tag = 0;
-            unsigned long long *src = nullptr;
-            unsigned long long pre[IMP_REGS];
-            // every thread issues IMP_REGS loads in every step (a harmless read of the hyperplane
-            // table where there is no word to fetch), so that the number of loads in flight after
-            // the tables read a step ahead is fixed and waiting for those does not wait for these
-            const unsigned long long *pre_p[IMP_REGS];
-#pragma unroll
-            for (int u = 0; u < IMP_REGS; ++u) pre_p[u] = reinterpret_cast<const unsigned long long *>(pst);
-            if (a.NP == 2 && pi + 1 < H) {
-                const int nh = fwd ? h + 1 : h - 1;
-                // part 0 reads part 1 through +t (lower hyperplane: this sweep's values in a
-                // forward sweep); part 1 reads part 0 through -t (higher hyperplane)
-                const int ver = ((part == 0) == fwd) ? w : w - 1;
-                if (ver >= 0) {  // before the first sweep the halo is zero
-                    e0 = imps[nh];
-                    ne = imps[nh + 1] - e0;
-                    nw = 24 * ne;
-                    tag = xch_tag(epoch, ver);
-                    src = xi + (size_t)(ver % 3) * 24 * Hp;
-#pragma unroll
-                    for (int u = 0; u < IMP_REGS; ++u) {
-                        const int t = threadIdx.x + u * blockDim.x;
-                        if (t < nw) {
-                            const int c = t / ne, e = t - c * ne;
-                            pre_p[u] = src + (size_t)c * Hp + imp[e0 + e];
-                        }
-                    }
-                }
-            }
-#pragma unroll
-            for (int u = 0; u < IMP_REGS; ++u) pre[u] = xch_get(const_cast<unsigned long long *>(pre_p[u]));
-            // (2) the updates; a part-local site i of plane h sits at block slot
+            const int h = fwd ? pi : H - 1 - pi, hn = pi + 1 == H ? h : fwd ? h + 1 : h - 1;
+            // (1) the updates; a part-local site i of plane h sits at block slot
             // i + pst[h] + part (pst[h + 1] - pst[h]) (each part owns one contiguous slot
             // range of every hyperplane, part 0 first)
-            const int shift = a.NP == 2 ? pst[h] + part * (pst[h + 1] - pst[h]) : 0;
-            // At the turn of a sweep (w > 0, pi = 0) the plane repeats: the top corner of the
-            // sub-blocks after a forward sweep, the bottom corner after a backward one.  Every
-            // neighbour of such a site lies on the side just swept and has not changed since the
-            // site's last update, so with omega = 1 (no (1 - omega) x term) the update would give
-            // the same value bit for bit: it is skipped and only the boundary words are
-            // published again under the new sweep's tag.
-            const bool repeat = omega == 1.f && w > 0 && pi == 0;
-            auto update = [&](int i, uint2 nb, uint2 gl, int kx) {
-                const int s = i + shift;
-                cx<float> xn[6];
-                if (repeat) {
-#pragma unroll
-                    for (int q = 0; q < 3; ++q) {
-                        const float4 f = xs[(3 * d + q) * NS + i];
-                        xn[2 * q] = {f.x, f.y};
-                        xn[2 * q + 1] = {f.z, f.w};
+            if (wv < a.sweep_waves) {
+                const int i_lo = at(pl0, h), i_hi = at(pl1, h), shift = NP == 2 ? i_lo + part * (i_hi - i_lo) : 0;
+                // this thread's first site with the tables read a step ahead, then those of the
+                // coming step (at a turn the plane repeats, and so do its tables), then any further
+                // sites (a hyperplane with more sites than the workgroup has lane pairs)
+                const uint2 nb0 = nb_n, gl0 = gl_n;
+                const int kx0 = kx_n, i0 = i_lo + q0, ns = 32 * a.sweep_waves;
+                tables_for(hn);
+                // At the turn of a sweep (w > 0, pi = 0) the plane repeats: the top corner of the
+                // sub-blocks after a forward sweep, the bottom corner after a backward one.  Every
+                // neighbour of such a site lies on the side just swept and has not changed since
+                // the site's last update, so with omega = 1 (no (1 - omega) x term) the update
+                // would give the same value bit for bit: it is skipped and only the boundary
+                // words are published again under the new sweep's tag.
+                if (omega == 1.f && w > 0 && pi == 0) {
+                    for (int i = i0; NP == 2 && i < i_hi; i += ns) {
+                        cx<float> xn[6];
+                        lds_get6(xn, xs, d, i);
+                        publish(xn, i == i0 ? kx0 : expi[i], w);
                     }
                 } else {
-                cx<float> out[6], v[6];
-                block_hop_clover_v<STAGED>(out, v, vb, xs, NS, nb, gl, U, Fk, ib, s, d, Vb, sg);
+                    auto update = [&](int i, uint2 nb, uint2 gl, int kx) {
+                        cx<float> out[6], v[6], xn[6];
+                        block_hop_clover_v<STAGED>(out, v, vb, xs, nb, gl, U, Fk, ib, i + shift, d, Vb, sg);
 #pragma unroll
-                for (int q = 0; q < 3; ++q) {
-                    float4 *o = &xs[(3 * d + q) * NS + i];
-                    const float4 ov = *o;
-                    const cx<float> n0 = v[2 * q] + kappa * out[2 * q], n1 = v[2 * q + 1] + kappa * out[2 * q + 1];
-                    xn[2 * q] = {(1.f - omega) * ov.x + omega * n0.r, (1.f - omega) * ov.y + omega * n0.i};
-                    xn[2 * q + 1] = {(1.f - omega) * ov.z + omega * n1.r, (1.f - omega) * ov.w + omega * n1.i};
-                    *o = make_float4(xn[2 * q].r, xn[2 * q].i, xn[2 * q + 1].r, xn[2 * q + 1].i);
-                }
-                }
-                if (kx >= 0) {
-                    const unsigned wt = xch_tag(epoch, w);
-                    unsigned long long *dst = xo + (size_t)(w % 3) * 24 * Hp + kx;
+                        for (int e = 0; e < 6; ++e) xn[e] = v[e] + kappa * out[e];
+                        if (omega != 1.f) {
+                            cx<float> ov[6];
+                            lds_get6(ov, xs, d, i);
 #pragma unroll
-                    for (int e = 0; e < 6; ++e) {
-                        xch_put(dst + (size_t)(12 * d + 2 * e) * Hp, xn[e].r, wt);
-                        xch_put(dst + (size_t)(12 * d + 2 * e + 1) * Hp, xn[e].i, wt);
-                    }
+                            for (int e = 0; e < 6; ++e)
+                                xn[e] = {(1.f - omega) * ov[e].r + omega * xn[e].r, (1.f - omega) * ov[e].i + omega * xn[e].i};
+                        }
+                        lds_put6(xs, d, i, xn);
+                        if constexpr (NP == 2) publish(xn, kx, w);
+                    };
+                    if (i0 < i_hi) update(i0, nb0, gl0, kx0);
+                    for (int i = i0 + ns; i < i_hi; i += ns) update(i, pnb[2 * i + d], gnb[i], NP == 2 ? expi[i] : -1);
                 }
-            };
-            // this thread's first site with the tables read a step ahead, then those of the
-            // coming step (at a turn the plane repeats, and so do its tables), then any further
-            // sites (a hyperplane with more sites than the workgroup has lane pairs)
-            const uint2 nb0 = nb_n, gl0 = gl_n;
-            const int kx0 = kx_n, i0 = pst[h] + q0;
-            if (i0 < pst[h + 1]) update(i0, nb0, gl0, kx0);
-            if (pi + 1 < H) tables_for(fwd ? h + 1 : h - 1);
-            for (int i = i0 + nq; i < pst[h + 1]; i += nq)
-                update(i, pnb[2 * i + d], gnb[i], a.NP == 2 ? expi[i] : -1);
-            // (3) the halo words into LDS
-            if (nw) {
-#pragma unroll
-                for (int u = 0; u < IMP_REGS; ++u) {
-                    const int t = threadIdx.x + u * blockDim.x;
-                    if (t < nw) {
-                        const int c = t / ne, e = t - c * ne, k = imp[e0 + e];
-                        unsigned long long *p = src + (size_t)c * Hp + k;
-                        xsf[(((c >> 2) * NS) + Vp + k) * 4 + (c & 3)] = xch_wait(pre[u], p, tag, gave_up, a);
-                    }
-                }
-                for (int t = threadIdx.x + IMP_REGS * blockDim.x; t < nw; t += blockDim.x) {
-                    const int c = t / ne, e = t - c * ne, k = imp[e0 + e];
-                    unsigned long long *p = src + (size_t)c * Hp + k;
-                    xsf[(((c >> 2) * NS) + Vp + k) * 4 + (c & 3)] = xch_wait(xch_get(p), p, tag, gave_up, a);
+            }
+            // (2) the halo words that the next step reads (each by one site of its plane, so they
+            // can be stored while others update), by a wave of their own where the workgroup has
+            // room for one: 2700 of the 13000 cycles of a step went into every wave copying a
+            // share of them.  A wave that does both updates first, since the other part may be
+            // waiting for what it publishes.  At the turn of a sweep the plane repeats and its halo
+            // slots already hold the right sweep (or the plane reads none), so nothing is fetched.
+            if (NP == 2 && wv == a.halo_wave) {
+                // part 0 reads part 1 through +t (lower hyperplane: this sweep's values in a
+                // forward sweep); part 1 reads part 0 through -t (higher hyperplane); before the
+                // first sweep the halo is zero
+                const int ver = ((part == 0) == fwd) ? w : w - 1;
+                if (pi + 1 < H && ver >= 0) {
+                    const int e0 = at(im0, hn);
+                    import_words(at(im1, hn) - e0, [&](int e) { return imp[e0 + e]; }, (ver % 3) * 24 * Hp, xch_tag(epoch, ver));
                 }
             }
             lds_barrier();
@@ -305,25 +292,20 @@ __global__ void __launch_bounds__(512) k_sap_phase_parts(GeomDev g, PartArgs a, 
     }
 
     // 3. the whole halo at the last sweep, then outputs
-    if (a.NP == 2) {
+    if (NP == 2) {
+        const int src = ((nsw - 1) % 3) * 24 * Hp;
         const unsigned tag = xch_tag(epoch, nsw - 1);
-        unsigned long long *src = xi + (size_t)((nsw - 1) % 3) * 24 * Hp;
-        for (int t = threadIdx.x; t < 24 * Hp; t += blockDim.x) {
-            const int c = t / Hp, k = t - c * Hp;
-            unsigned long long *p = src + (size_t)c * Hp + k;
-            xsf[(((c >> 2) * NS) + Vp + k) * 4 + (c & 3)] = xch_wait(xch_get(p), p, tag, gave_up, a);
-        }
+        for (int c = wv; c < 24; c += nwv)
+            for (int k = lane; k < Hp; k += 64) {
+                unsigned long long *p = xi + (src + c * Hp + k);
+                xsf[24 * (Vp + k) + c] = xch_wait(xch_get(p), p, tag, gave_up, a);
+            }
         __syncthreads();
     }
     for (int i = q0; i < Vp; i += nq) {
         const int s = gslot[i];
         cx<float> xv[6];
-#pragma unroll
-        for (int q = 0; q < 3; ++q) {
-            const float4 f = xs[(3 * d + q) * NS + i];
-            xv[2 * q] = {f.x, f.y};
-            xv[2 * q + 1] = {f.z, f.w};
-        }
+        lds_get6(xv, xs, d, i);
         store6(x, ib, s, d, Vb, xv);
         if (a.ssor_only) continue;
         cx<float> yv[6];
@@ -337,14 +319,14 @@ __global__ void __launch_bounds__(512) k_sap_phase_parts(GeomDev g, PartArgs a, 
         }
         store6(y, ib, s, d, Vb, yv);
         cx<float> out[6], v[6];
-        block_hop_clover_v<STAGED>(out, v, r, xs, NS, pnb[2 * i + d], gnb[i], U, Fk, ib, s, d, Vb, sg);
+        block_hop_clover_v<STAGED>(out, v, r, xs, pnb[2 * i + d], gnb[i], U, Fk, ib, s, d, Vb, sg);
 #pragma unroll
         for (int e = 0; e < 6; ++e) v[e] = v[e] - xv[e] + kappa * out[e];
         store6(r, ib, s, d, Vb, v);
     }
 
     // 4. the last workgroup to finish resets the ticket counter and advances the epoch
-    if (a.NP == 2) {
+    if (NP == 2) {
         __syncthreads();
         if (threadIdx.x == 0) {
             const unsigned done = atomicAdd(&a.sync[1], 1u);
@@ -405,6 +387,16 @@ void launch_sap_face_2l(Ctx *c, int colour, void *r, const void *x) {
                                          (const typename Prec<P_>::S2 *)c->Fin)));
 }
 
+template <int P> static void *parts_kernel(int np, bool staged) {
+    return np == 2 ? (staged ? (void *)k_sap_phase_parts<P, 2, true> : (void *)k_sap_phase_parts<P, 2, false>)
+                   : (staged ? (void *)k_sap_phase_parts<P, 1, true> : (void *)k_sap_phase_parts<P, 1, false>);
+}
+static void *parts_kernel(const Ctx *c) {
+    void *fn = nullptr;
+    INNER_SWITCH(c->prm.prec_inner, fn = parts_kernel<P_>(c->sap_np, c->parts_staged));
+    return fn;
+}
+
 void launch_sap_phase_parts(Ctx *c, int colour, int gather, int first, int ssor_only, const void *rsrc, void *r,
                             void *x, void *y) {
     PartArgs a;
@@ -415,7 +407,6 @@ void launch_sap_phase_parts(Ctx *c, int colour, int gather, int first, int ssor_
     a.n_ssor = c->prm.n_ssor;
     a.kappa = (float)c->prm.kappa;
     a.omega = (float)c->prm.omega;
-    a.NP = c->sap_np;
     a.Vp = c->part_Vp;
     a.Hp = c->part_Hp;
     a.gslot = c->part_gslot;
@@ -429,27 +420,21 @@ void launch_sap_phase_parts(Ctx *c, int colour, int gather, int first, int ssor_
     a.sync = c->xsync;
     a.spin_limit = c->halo_spin_limit;
     a.wait_xor = c->halo_wait_xor;
-    const dim3 grid(c->g.NBc * c->sap_np), block(c->part_threads);
-    INNER_SWITCH(c->prm.prec_inner, ({
-                     using S2 = typename Prec<P_>::S2;
-                     if (c->parts_staged)
-                         k_sap_phase_parts<P_, true><<<grid, block, c->parts_lds, c->stream>>>(
-                             c->g, a, (const S2 *)rsrc, (S2 *)r, (S2 *)x, (S2 *)y, (const S2 *)c->Uin, (const S2 *)c->Fin);
-                     else
-                         k_sap_phase_parts<P_, false><<<grid, block, c->parts_lds, c->stream>>>(
-                             c->g, a, (const S2 *)rsrc, (S2 *)r, (S2 *)x, (S2 *)y, (const S2 *)c->Uin, (const S2 *)c->Fin);
-                 }));
+    // two lanes per site of the widest hyperplane, and for a split block a wave for the halo words
+    // (the last one does both where the sweeps take all eight)
+    a.sweep_waves = c->part_threads / 64;
+    const int waves = c->sap_np == 2 ? std::min(8, a.sweep_waves + 1) : a.sweep_waves;
+    a.halo_wave = waves - 1;
+    const dim3 grid(c->g.NBc * c->sap_np), block(64 * waves);
+    void *fn = parts_kernel(c);
+    GeomDev g = c->g;
+    void *args[] = {&g, &a, &rsrc, &r, &x, &y, &c->Uin, &c->Fin};
+    (void)hipLaunchKernel(fn, grid, block, args, c->parts_lds, c->stream);
 }
 
 int set_parts_lds_limit(Ctx *c) {
     if (!c->use_parts || c->parts_lds <= 65536) return 0;
-    const int bytes = (int)c->parts_lds;
-    INNER_SWITCH(c->prm.prec_inner, ({
-                     (void)hipFuncSetAttribute((const void *)k_sap_phase_parts<P_, true>,
-                                               hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
-                     (void)hipFuncSetAttribute((const void *)k_sap_phase_parts<P_, false>,
-                                               hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
-                 }));
+    (void)hipFuncSetAttribute(parts_kernel(c), hipFuncAttributeMaxDynamicSharedMemorySize, (int)c->parts_lds);
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 

@@ -61,6 +61,15 @@ template <typename S2> __device__ __forceinline__ unsigned to_raw(cx<float> v) {
     st(&o, v);
     return raw2(o);
 }
+// the iterate of this kernel is planar, float4 [6][NS]
+__device__ __forceinline__ void lds_planar(cx<float> psi[12], const float4 *xs, int NS, int slot) {
+#pragma unroll
+    for (int q = 0; q < 6; ++q) {
+        const float4 f = xs[q * NS + slot];
+        psi[2 * q] = {f.x, f.y};
+        psi[2 * q + 1] = {f.z, f.w};
+    }
+}
 // keeps the compiler from hoisting what it derives from w (conversions, third link rows) out of
 // the sweep loop, where it would have to spill them
 __device__ __forceinline__ void opaque(unsigned &w) { asm volatile("" : "+v"(w)); }
@@ -130,7 +139,7 @@ template <typename S2, int NS, int D>
 __device__ __forceinline__ void eo_hop(cx<float> acc[12], const EoSite &q, uint4 nb, const float4 *xs) {
     const unsigned w = D < 4 ? (D < 2 ? nb.x : nb.y) : (D < 6 ? nb.z : nb.w);
     cx<float> psi[12], u[9];
-    lds_spinor(psi, xs, NS, (int)(D % 2 ? w >> 16 : w & 0xffffu));
+    lds_planar(psi, xs, NS, (int)(D % 2 ? w >> 16 : w & 0xffffu));
 #pragma unroll
     for (int e = 0; e < 6; ++e) u[e] = from_raw<S2>(q.u[D][e]);
     hop_site<D / 2, D % 2 == 1, D == 0>(acc, psi, u);
@@ -349,7 +358,7 @@ __device__ __forceinline__ void eo_phase(const GeomDev &g, const EoTables &t, fl
         for (int c = 0; c < 12; ++c) v[c] = from_raw<S2>(rw[c]);
         if (mode & EO_GATHER) {
             cx<float> h[12], fh[12];
-            lds_spinor(h, xs, NS, s);
+            lds_planar(h, xs, NS, s);
             eo_clover<S2>(fh, h, q);
 #pragma unroll
             for (int c = 0; c < 12; ++c) v[c] = rfma(kappa, fh[c], v[c]);
@@ -383,7 +392,7 @@ __device__ __forceinline__ void eo_phase(const GeomDev &g, const EoTables &t, fl
     }
     auto finish = [&](const unsigned *yw, int s) {
         cx<float> xv[12], yv[12];
-        lds_spinor(xv, xs, NS, s);
+        lds_planar(xv, xs, NS, s);
         store_spinor(x, g, ib, s, xv);
         if (mode & EO_SSOR_ONLY) return;
 #pragma unroll
@@ -403,7 +412,7 @@ __device__ __forceinline__ void eo_phase(const GeomDev &g, const EoTables &t, fl
     if (mode & EO_SSOR_ONLY) return;
     cx<float> v[12], xv[12];
     eo_update<S2, NS>(v, qo, t, xs, vo, n, so, kappa);
-    lds_spinor(xv, xs, NS, so);
+    lds_planar(xv, xs, NS, so);
 #pragma unroll
     for (int c = 0; c < 12; ++c) {
         v[c] = v[c] - xv[c];

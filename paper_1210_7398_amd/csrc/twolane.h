@@ -1,8 +1,7 @@
 // Two lanes per site: the per-site building blocks of the two-lane SAP phase kernels (one
 // source, csrc/sap_parts.hip; several sources, csrc/batch.hip).  Lane d = 0 of a pair takes
 // the four forward hops (1 - gamma_mu) U_mu(n) psi(n + mu), lane d = 1 the four backward hops
-// (1 + gamma_mu) U_mu(n - mu)^+ psi(n - mu), with U_mu(n - mu) read at the neighbour and
-// daggered in registers; both lanes run the same instructions (projection sign s = +1 / -1).
+// (1 + gamma_mu) U_mu(n - mu)^+ psi(n - mu), with U_mu(n - mu) read at the neighbour; both lanes run the same instructions (projection sign s = +1 / -1).
 // A pair butterfly adds the two halves, and lane d then owns chiral half d (spins 2d, 2d + 1).
 #pragma once
 
@@ -10,31 +9,38 @@
 
 namespace sapq {
 
-// (1 - s gamma_mu) M psi accumulated into acc, M a full SU(3) matrix; the projection and
-// the rebuild of the lower spins follow the chiral-basis gamma matrices (see sitecore.h).
-// The helpers below are written for the compute type C (float, or double for the FP64
-// operator); the SSOR iterate in LDS is always float.
-template <int MU, typename C>
+// (1 - s gamma_mu) W psi accumulated into acc (FIRST: acc is set), W = U on the lanes with s = 1 and
+// U^+ on those with s = -1, by the same instructions on both; the projection and the rebuild of
+// the lower spins follow the chiral-basis gamma matrices (see sitecore.h).  The backward lanes
+// work on conjugates, conj(U^+ h) = U^T conj(h): the transpose is a swap of the off-diagonal
+// elements (link_swap), and the sign of the imaginary parts rides on the multiply-adds of the
+// projection and of the sums, which take a factor s anyway (conjugating the link itself took
+// nine more instructions per hop).  The helpers below are written for the compute type C (float,
+// or double for the FP64 operator); the SSOR iterate in LDS is always float.
+template <int MU, bool FIRST, typename C>
 __device__ __forceinline__ void hop_lane(cx<C> acc[12], const cx<C> psi[12], const cx<C> u[9], C s) {
-    cx<C> h0[3], h1[3], g0[3], g1[3];
+    cx<C> h0[3], h1[3], g0[3], g1[3];  // conjugated where s = -1
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
         const cx<C> p0 = psi[a], p1 = psi[3 + a], p2 = psi[6 + a], p3 = psi[9 + a];
-        if (MU == 0) { h0[a] = rfma(s, itimes(p3), p0);  h1[a] = rfma(s, itimes(p2), p1); }
-        if (MU == 1) { h0[a] = rfma(s, p3, p0);          h1[a] = rfma(-s, p2, p1); }
-        if (MU == 2) { h0[a] = rfma(s, itimes(p2), p0);  h1[a] = rfma(-s, itimes(p3), p1); }
-        if (MU == 3) { h0[a] = rfma(-s, p2, p0);         h1[a] = rfma(-s, p3, p1); }
+        if (MU == 0) { h0[a] = {fmx(-s, p3.i, p0.r), fmx(s, p0.i, p3.r)}; h1[a] = {fmx(-s, p2.i, p1.r), fmx(s, p1.i, p2.r)}; }
+        if (MU == 1) { h0[a] = {fmx(s, p3.r, p0.r), fmx(s, p0.i, p3.i)};  h1[a] = {fmx(-s, p2.r, p1.r), fmx(s, p1.i, -p2.i)}; }
+        if (MU == 2) { h0[a] = {fmx(-s, p2.i, p0.r), fmx(s, p0.i, p2.r)}; h1[a] = {fmx(s, p3.i, p1.r), fmx(s, p1.i, -p3.r)}; }
+        if (MU == 3) { h0[a] = {fmx(-s, p2.r, p0.r), fmx(s, p0.i, -p2.i)}; h1[a] = {fmx(-s, p3.r, p1.r), fmx(s, p1.i, -p3.i)}; }
     }
     su3_mul(g0, u, h0, false);
     su3_mul(g1, u, h1, false);
+    // acc + (x, y) or acc + (s x, y), (x, s y) with a sign
+    auto ps = [&](cx<C> &o, C x, C y) { o = FIRST ? cx<C>{x, s * y} : cx<C>{o.r + x, fmx(s, y, o.i)}; };
+    auto sp = [&](cx<C> &o, C x, C y) { o = FIRST ? cx<C>{s * x, y} : cx<C>{fmx(s, x, o.r), o.i + y}; };
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
-        acc[a] = acc[a] + g0[a];
-        acc[3 + a] = acc[3 + a] + g1[a];
-        if (MU == 0) { acc[6 + a] = rfma(-s, itimes(g1[a]), acc[6 + a]); acc[9 + a] = rfma(-s, itimes(g0[a]), acc[9 + a]); }
-        if (MU == 1) { acc[6 + a] = rfma(-s, g1[a], acc[6 + a]);         acc[9 + a] = rfma(s, g0[a], acc[9 + a]); }
-        if (MU == 2) { acc[6 + a] = rfma(-s, itimes(g0[a]), acc[6 + a]); acc[9 + a] = rfma(s, itimes(g1[a]), acc[9 + a]); }
-        if (MU == 3) { acc[6 + a] = rfma(-s, g0[a], acc[6 + a]);         acc[9 + a] = rfma(-s, g1[a], acc[9 + a]); }
+        ps(acc[a], g0[a].r, g0[a].i);
+        ps(acc[3 + a], g1[a].r, g1[a].i);
+        if (MU == 0) { ps(acc[6 + a], g1[a].i, -g1[a].r);  ps(acc[9 + a], g0[a].i, -g0[a].r); }
+        if (MU == 1) { sp(acc[6 + a], -g1[a].r, -g1[a].i); sp(acc[9 + a], g0[a].r, g0[a].i); }
+        if (MU == 2) { ps(acc[6 + a], g0[a].i, -g0[a].r);  ps(acc[9 + a], -g1[a].i, g1[a].r); }
+        if (MU == 3) { sp(acc[6 + a], -g0[a].r, -g0[a].i); sp(acc[9 + a], -g1[a].r, -g1[a].i); }
     }
 }
 
@@ -47,16 +53,16 @@ __device__ __forceinline__ void link_rows(cx<C> u[9], const S2 *p, int Vb) {
     link_rebuild(u);
 }
 
-// u <- u^+ on the lanes with dag set, u unchanged on the others (same instructions on both)
-template <typename C> __device__ __forceinline__ void dagger_if(cx<C> u[9], bool dag) {
-    cx<C> t[9];
+// u <- u^T on the lanes with swap set, u unchanged on the others (same instructions on both)
+template <typename C> __device__ __forceinline__ void link_swap(cx<C> u[9], bool swap) {
 #pragma unroll
     for (int a = 0; a < 3; ++a)
 #pragma unroll
-        for (int b = 0; b < 3; ++b) t[3 * a + b] = sel(dag, u[3 * b + a], u[3 * a + b]);
-    const C sg = dag ? C(-1) : C(1);
-#pragma unroll
-    for (int e = 0; e < 9; ++e) u[e] = {t[e].r, sg * t[e].i};
+        for (int b = a + 1; b < 3; ++b) {
+            const cx<C> up = u[3 * a + b], lo = u[3 * b + a];
+            u[3 * a + b] = sel(swap, lo, up);
+            u[3 * b + a] = sel(swap, up, lo);
+        }
 }
 
 // one hermitian chiral block [[A, B], [B^+, C]] of F (18 slots, see k_pack_clover)
@@ -112,27 +118,42 @@ __device__ __forceinline__ void store6(S2 *f, int ib, int s, int d, int Vb, cons
     for (int e = 0; e < 6; ++e) st(p + (size_t)e * Vb, v[e]);
 }
 
-// iterate in LDS: float4 [6][NS], float4 q holding components 2q and 2q + 1
-__device__ __forceinline__ void lds_spinor(cx<float> psi[12], const float4 *xs, int NS, int slot) {
+// iterate in LDS: records of six float4 per slot, float4 q holding components 2q and 2q + 1, so
+// that a neighbour's six reads share one address (eight lanes of a 16-byte read, the LDS's width,
+// start at eight different banks whenever their slots are consecutive)
+__device__ __forceinline__ void lds_spinor(cx<float> psi[12], const float4 *xs, int slot) {
 #pragma unroll
     for (int q = 0; q < 6; ++q) {
-        const float4 f = xs[q * NS + slot];
+        const float4 f = xs[6 * slot + q];
         psi[2 * q] = {f.x, f.y};
         psi[2 * q + 1] = {f.z, f.w};
     }
 }
+// lane d's half of the record (components 6d .. 6d + 5)
+__device__ __forceinline__ void lds_get6(cx<float> v[6], const float4 *xs, int d, int slot) {
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+        const float4 f = xs[6 * slot + 3 * d + q];
+        v[2 * q] = {f.x, f.y};
+        v[2 * q + 1] = {f.z, f.w};
+    }
+}
+__device__ __forceinline__ void lds_put6(float4 *xs, int d, int slot, const cx<float> v[6]) {
+#pragma unroll
+    for (int q = 0; q < 3; ++q)
+        xs[6 * slot + 3 * d + q] = make_float4(v[2 * q].r, v[2 * q].i, v[2 * q + 1].r, v[2 * q + 1].i);
+}
 
 // One in-block hop of the lane: the neighbour spinor from LDS slot `slot` and the lane's
-// link rows u (U_mu at the site for lane 0, at the backward neighbour for lane 1, where they
-// are daggered), already loaded.
-template <int MU>
-__device__ __forceinline__ void lds_hop(cx<float> acc[12], const float4 *xs, int NS, unsigned slot, cx<float> u[9],
+// link rows u (U_mu at the site for lane 0, at the backward neighbour for lane 1), already loaded.
+template <int MU, bool FIRST = false>
+__device__ __forceinline__ void lds_hop(cx<float> acc[12], const float4 *xs, unsigned slot, cx<float> u[9],
                                         float sg) {
     cx<float> psi[12];
-    lds_spinor(psi, xs, NS, (int)slot);
+    lds_spinor(psi, xs, (int)slot);
     link_rebuild(u);
-    dagger_if(u, sg < 0.f);
-    hop_lane<MU>(acc, psi, u, sg);
+    link_swap(u, sg < 0.f);
+    hop_lane<MU, FIRST>(acc, psi, u, sg);
 }
 
 // the six stored rows of link U_mu at block slot sl of block ib
@@ -154,11 +175,9 @@ __device__ __forceinline__ void link_load(cx<float> u[9], const S2 *U, int ib, i
 // latency exposed.  Both orders compute the same values.
 template <bool WITH_V, bool STAGED, typename S2>
 __device__ __forceinline__ void block_hop_clover_impl(cx<float> out[6], cx<float> v[6], const S2 *vf, const float4 *xs,
-                                                      int NS, uint2 nb, uint2 gl, const S2 *U, const S2 *Fk, int ib,
+                                                      uint2 nb, uint2 gl, const S2 *U, const S2 *Fk, int ib,
                                                       int s, int d, int Vb, float sg) {
     cx<float> acc[12];
-#pragma unroll
-    for (int c = 0; c < 12; ++c) acc[c] = cxz<float>();
     const bool at_site = d == 0;
     const int sl[4] = {at_site ? s : (int)(gl.x & 0xffffu), at_site ? s : (int)(gl.x >> 16),
                        at_site ? s : (int)(gl.y & 0xffffu), at_site ? s : (int)(gl.y >> 16)};
@@ -169,15 +188,15 @@ __device__ __forceinline__ void block_hop_clover_impl(cx<float> out[6], cx<float
         for (int m = 0; m < 4; ++m) link_load(u[m], U, ib, m, sl[m], Vb);
     }
     if constexpr (!STAGED) link_load(u[0], U, ib, 0, sl[0], Vb);
-    lds_hop<0>(acc, xs, NS, nb.x & 0xffffu, u[0], sg);
+    lds_hop<0, true>(acc, xs, nb.x & 0xffffu, u[0], sg);
     if constexpr (!STAGED) link_load(u[1], U, ib, 1, sl[1], Vb);
-    lds_hop<1>(acc, xs, NS, nb.x >> 16, u[1], sg);
+    lds_hop<1>(acc, xs, nb.x >> 16, u[1], sg);
     if constexpr (STAGED) load_clov(F, Fk + s, Vb);
     if constexpr (!STAGED) link_load(u[2], U, ib, 2, sl[2], Vb);
-    lds_hop<2>(acc, xs, NS, nb.y & 0xffffu, u[2], sg);
+    lds_hop<2>(acc, xs, nb.y & 0xffffu, u[2], sg);
     if constexpr (STAGED && WITH_V) load6(v, vf, ib, s, d, Vb);
     if constexpr (!STAGED) link_load(u[3], U, ib, 3, sl[3], Vb);
-    lds_hop<3>(acc, xs, NS, nb.y >> 16, u[3], sg);
+    lds_hop<3>(acc, xs, nb.y >> 16, u[3], sg);
     pair_reduce(acc);
     if constexpr (!STAGED) {
         load_clov(F, Fk + s, Vb);
@@ -189,24 +208,24 @@ __device__ __forceinline__ void block_hop_clover_impl(cx<float> out[6], cx<float
     clover_apply(out, own, F);
 }
 template <typename S2>
-__device__ __forceinline__ void block_hop_clover(cx<float> out[6], const float4 *xs, int NS, uint2 nb, uint2 gl,
+__device__ __forceinline__ void block_hop_clover(cx<float> out[6], const float4 *xs, uint2 nb, uint2 gl,
                                                  const S2 *U, const S2 *Fk, int ib, int s, int d, int Vb, float sg) {
-    block_hop_clover_impl<false, true>(out, (cx<float> *)nullptr, (const S2 *)nullptr, xs, NS, nb, gl, U, Fk, ib, s, d,
+    block_hop_clover_impl<false, true>(out, (cx<float> *)nullptr, (const S2 *)nullptr, xs, nb, gl, U, Fk, ib, s, d,
                                        Vb, sg);
 }
 // the unstaged order
 template <typename S2>
-__device__ __forceinline__ void block_hop_clover_seq(cx<float> out[6], const float4 *xs, int NS, uint2 nb, uint2 gl,
+__device__ __forceinline__ void block_hop_clover_seq(cx<float> out[6], const float4 *xs, uint2 nb, uint2 gl,
                                                      const S2 *U, const S2 *Fk, int ib, int s, int d, int Vb, float sg) {
-    block_hop_clover_impl<false, false>(out, (cx<float> *)nullptr, (const S2 *)nullptr, xs, NS, nb, gl, U, Fk, ib, s, d,
+    block_hop_clover_impl<false, false>(out, (cx<float> *)nullptr, (const S2 *)nullptr, xs, nb, gl, U, Fk, ib, s, d,
                                         Vb, sg);
 }
 // the same and v = the lane's six components of vf at (ib, s), in either order
 template <bool STAGED, typename S2>
 __device__ __forceinline__ void block_hop_clover_v(cx<float> out[6], cx<float> v[6], const S2 *vf, const float4 *xs,
-                                                   int NS, uint2 nb, uint2 gl, const S2 *U, const S2 *Fk, int ib, int s,
+                                                   uint2 nb, uint2 gl, const S2 *U, const S2 *Fk, int ib, int s,
                                                    int d, int Vb, float sg) {
-    block_hop_clover_impl<true, STAGED>(out, v, vf, xs, NS, nb, gl, U, Fk, ib, s, d, Vb, sg);
+    block_hop_clover_impl<true, STAGED>(out, v, vf, xs, nb, gl, U, Fk, ib, s, d, Vb, sg);
 }
 
 // one hop leaving the block (neighbour in another block, from the global iterate x)
@@ -224,12 +243,13 @@ __device__ __forceinline__ void gather_hop(cx<float> acc[12], const GeomDev &g, 
     for (int c = 0; c < 12; ++c) psi[c] = ph * psi[c];
     const bool at_site = d == 0;
     link_rows(u, U + ((size_t)(at_site ? ib : ibn) * 4 + MU) * 6 * g.Vb + (at_site ? s : sn), g.Vb);
-    dagger_if(u, d != 0);
-    hop_lane<MU>(acc, psi, u, sg);
+    link_swap(u, d != 0);
+    hop_lane<MU, false>(acc, psi, u, sg);
 }
 
 // one hop of the lane to a neighbour inside or outside the block, read from the global field x
-// (the full operator); outside neighbours across the lattice boundary take the fermion phase
+// (the full operator; the hop of MU = 0 sets acc); outside neighbours across the lattice boundary
+// take the fermion phase
 template <int MU, typename S2, typename C>
 __device__ __forceinline__ void hop_any(cx<C> acc[12], const GeomDev &g, const S2 *x, const S2 *U, int ib, int s, int d,
                                         C sg) {
@@ -249,8 +269,8 @@ __device__ __forceinline__ void hop_any(cx<C> acc[12], const GeomDev &g, const S
     for (int c = 0; c < 12; ++c) psi[c] = ph * psi[c];
     const bool at_site = d == 0;
     link_rows(u, U + ((size_t)(at_site ? ib : ibn) * 4 + MU) * 6 * g.Vb + (at_site ? s : sn), g.Vb);
-    dagger_if(u, d != 0);
-    hop_lane<MU>(acc, psi, u, sg);
+    link_swap(u, d != 0);
+    hop_lane<MU, MU == 0>(acc, psi, u, sg);
 }
 
 }  // namespace sapq
