@@ -469,10 +469,8 @@ int sapq_dslash(sapq_ctx *h, double *out, const double *in, int prec) {
     int rc = ready(c);
     if (rc) return rc;
     void *a = prec == SAPQ_FP64 ? (void *)c->d_tmp : c->i_tmp;
-    void *b = prec == SAPQ_FP64 ? (void *)c->d_v : c->i_v;
     launch_pack_spinor(c, prec, a, in, 1.0);
-    launch_dslash(c, prec, b, a);
-    launch_unpack_spinor(c, prec, out, b, 1.0);
+    launch_dslash_lex(c, prec, out, a);
     return hipcheck(hipGetLastError(), "sapq_dslash");
 }
 

@@ -1,5 +1,5 @@
-// The allocation-free variant of sapq_dslash (sapq_dslash_noalloc): its two staging vectors
-// (the operand and the result in the internal layout) live in a static device array of the
+// The allocation-free variant of sapq_dslash (sapq_dslash_noalloc): its staging vector
+// (the operand in the internal layout) lives in a static device array of the
 // library instead of the context's arena, so a caller that cannot allocate (graph capture, a
 // serving loop) needs no buffer of its own beyond its input and output.
 //
@@ -57,6 +57,8 @@ extern "C" int sapq_dslash_noalloc(sapq_ctx *h, double *out, const double *in, i
     Ctx *c = &h->c;
     if (prec != SAPQ_FP64 && prec != c->prm.prec_inner) { set_error("prec must be SAPQ_FP64 or the context's prec_inner"); return SAPQ_EINVAL; }
     if (out == in) { set_error("in and out may not alias"); return SAPQ_EINVAL; }
+    // Two vectors bound the lattice, of which the operator, writing its result in the interchange
+    // layout, now stages one: the documented limit stays what callers know.
     const size_t vec = ((c->nvec * elem_bytes(prec)) + 255) & ~(size_t)255;
     if (2 * vec > NOALLOC_SCRATCH_BYTES) {
         set_error("sapq_dslash_noalloc: the lattice needs " + std::to_string(2 * vec) + " bytes of staging, beyond the " +
@@ -66,10 +68,8 @@ extern "C" int sapq_dslash_noalloc(sapq_ctx *h, double *out, const double *in, i
     if (!c->have_U || !c->have_F) { set_error("gauge field and clover field must be loaded first"); return SAPQ_ESTATE; }
     char *base = (char *)scratch_of(c->device);
     if (!base) { set_error("no static scratch address for the context's device"); return SAPQ_ESTATE; }
-    void *a = base, *b = base + vec;
-    launch_pack_spinor(c, prec, a, in, 1.0);
-    launch_dslash(c, prec, b, a);
-    launch_unpack_spinor(c, prec, out, b, 1.0);
+    launch_pack_spinor(c, prec, base, in, 1.0);
+    launch_dslash_lex(c, prec, out, base);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) {
         set_error(std::string("sapq_dslash_noalloc: ") + hipGetErrorString(e));

@@ -181,6 +181,7 @@ int launch_pack_links(Ctx *c, const double *U, double *max_dev);
 void launch_pack_clover(Ctx *c, const double *F);
 bool launch_permute_fields(Ctx *c, const int *perm);
 void launch_dslash(Ctx *c, int prec, void *out, const void *in);
+void launch_dslash_lex(Ctx *c, int prec, double *out, const void *in);  // out in the interchange layout
 // first / last: the phase belongs to the first / last of the M_SAP cycles (first: rsrc is not r)
 void launch_sap_phase(Ctx *c, int colour, bool first, bool last, const void *rsrc, void *r, void *x, void *y);
 void launch_sap_face(Ctx *c, int colour, void *r, const void *x);

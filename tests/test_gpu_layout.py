@@ -1,7 +1,7 @@
 """Layout conversion of spinor fields (k_pack_spinor, k_unpack_spinor and their difference
-form): with F = 0 the operator and M_SAP are the identity, so every call must return its input
+form, and the operator's own output tile): with F = 0 the operator and M_SAP are the identity, so every call must return its input
 exactly, rounded to the storage precision (to FP16 and BF16 directly or through FP32).  Sizes
-around the kernels' tiles of 128 sites: a lattice that ends inside a tile, blocks of fewer and of
+around the kernels' tiles of 128 (FP64 operator: 64) sites: a lattice that ends inside a tile, blocks of fewer and of
 more sites than a tile, odd extents."""
 import numpy as np
 import pytest
@@ -11,7 +11,7 @@ from paper_1210_7398_amd import sapq, synth
 
 pytestmark = pytest.mark.gpu
 
-SHAPES = [((6, 4, 4, 6), (3, 2, 2, 3), (0, 0, 0, 0)), ((8, 4, 4, 8), (4, 2, 2, 4), (2, 2, 2, 2)),
+SHAPES = [((6, 4, 4, 6), (3, 2, 2, 3), (0, 0, 0, 0)), ((6, 6, 6, 6), (3, 3, 3, 3), (0, 0, 0, 0)), ((8, 4, 4, 8), (4, 2, 2, 4), (2, 2, 2, 2)),
           ((10, 8, 6, 12), (5, 4, 3, 6), (0, 0, 0, 0)), ((12, 12, 12, 24), (6, 6, 6, 12), (3, 3, 3, 6))]
 
 
