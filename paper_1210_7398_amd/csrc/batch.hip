@@ -255,7 +255,7 @@ __global__ void __launch_bounds__(768) k_bsap_phase_2l(const BatchDev *__restric
     if (!any) return;  // uniform over the workgroup
     const int tpr = F.tpr;
     const int k = threadIdx.x / tpr, tt = threadIdx.x - k * tpr;
-    const int d = tt & 1, q0 = tt >> 1, nq = tpr >> 1;
+    const int d = pair_dir(tt), q0 = pair_site(tt), nq = tpr >> 1;
     const int Vb = g.Vb;
     const bool live = k < NR && k0 + k < F.nrhs;
     float4 *xs = xb + (size_t)min(k, NR - 1) * 6 * (Vb + 1);
@@ -285,10 +285,8 @@ __global__ void __launch_bounds__(768) k_bsap_phase_2l(const BatchDev *__restric
                 gather_hop<1>(acc, g, x, U, ib, i, d, bl[1], sg);
                 gather_hop<2>(acc, g, x, U, ib, i, d, bl[2], sg);
                 gather_hop<3>(acc, g, x, U, ib, i, d, bl[3], sg);
-                pair_reduce(acc);
                 cx<float> own[6], out[6];
-#pragma unroll
-                for (int e = 0; e < 6; ++e) own[e] = sel(d != 0, acc[6 + e], acc[e]);
+                pair_reduce(own, acc);
                 clover_block(out, own, Fk + i, Vb);
 #pragma unroll
                 for (int e = 0; e < 6; ++e) v[e] = v[e] + kappa * out[e];
@@ -439,18 +437,17 @@ __global__ void __launch_bounds__(256) k_bsap_face_2l(const BatchDev *__restrict
     const BField &F = B.f[fi];
     if (k >= F.nrhs || bst[F.rhs0 + k].done) return;
     const GeomDev &g = F.g;
-    const long i = xcd_site_base(128) + (threadIdx.x >> 1);
-    const int d = threadIdx.x & 1;
+    const long i = xcd_site_base(128) + pair_site(threadIdx.x);
+    const int d = pair_dir(threadIdx.x);
     if (i >= (long)g.NBc * g.Vb) return;  // both lanes of a site together
     const int ib = colour * g.NBc + (int)(i / g.Vb), s = (int)(i % g.Vb);
-    int outside = 0;
+    bool outside = false;
 #pragma unroll
     for (int mu = 0; mu < 4; ++mu) {
         const unsigned w = g.nbr16[mu * g.Vb + s];
-        outside |= ((d ? (w >> 16) : w) & 0x8000u) ? 0 : 1;
+        outside |= !((d ? (w >> 16) : w) & 0x8000u);
     }
-    outside |= __builtin_amdgcn_update_dpp(0, outside, QUAD_XOR1, 0xF, 0xF, true);
-    if (!outside) return;
+    if (!pair_any(outside)) return;
     const size_t ko = (size_t)k * F.nvec;
     S2 *r = (S2 *)F.iv[s_r] + ko;
     const S2 *x = (const S2 *)F.iv[s_x] + ko;
@@ -463,10 +460,8 @@ __global__ void __launch_bounds__(256) k_bsap_face_2l(const BatchDev *__restrict
     gather_hop<1>(acc, g, x, U, ib, s, d, g.blk_nbr[(2 * 1 + d) * g.NB + ib], sg);
     gather_hop<2>(acc, g, x, U, ib, s, d, g.blk_nbr[(2 * 2 + d) * g.NB + ib], sg);
     gather_hop<3>(acc, g, x, U, ib, s, d, g.blk_nbr[(2 * 3 + d) * g.NB + ib], sg);
-    pair_reduce(acc);
     cx<float> own[6], out[6], v[6];
-#pragma unroll
-    for (int e = 0; e < 6; ++e) own[e] = sel(d != 0, acc[6 + e], acc[e]);
+    pair_reduce(own, acc);
     clover_block(out, own, (const S2 *)F.Fin + ((size_t)ib * 2 + d) * 18 * g.Vb + s, g.Vb);
     load6(v, r, ib, s, d, g.Vb);
 #pragma unroll

@@ -200,8 +200,8 @@ __global__ void __launch_bounds__(2 * dslash_sites(P)) k_dslash(GeomDev g, OUT *
     constexpr int N = dslash_sites(P);
     __shared__ S2 tile[LEX ? N * LAY_PITCH : 1];
     __shared__ int lex[LEX ? N : 1];
-    const long i0 = xcd_site_base(N), i = i0 + (threadIdx.x >> 1);
-    const int d = threadIdx.x & 1;
+    const long i0 = xcd_site_base(N), i = i0 + pair_site(threadIdx.x);
+    const int d = pair_dir(threadIdx.x);
     if (i < g.V) {
         const int bl = (int)(i / g.Vb), s = (int)(i - (long)bl * g.Vb);
         const int ib = g.lex_blk[bl];
@@ -211,17 +211,15 @@ __global__ void __launch_bounds__(2 * dslash_sites(P)) k_dslash(GeomDev g, OUT *
         hop_any<1>(acc, g, in, U, ib, s, d, sg);
         hop_any<2>(acc, g, in, U, ib, s, d, sg);
         hop_any<3>(acc, g, in, U, ib, s, d, sg);
-        pair_reduce(acc);
         cx<C> own[6], fh[6], v[6];
-#pragma unroll
-        for (int e = 0; e < 6; ++e) own[e] = sel(d != 0, acc[6 + e], acc[e]);
+        pair_reduce(own, acc);
         clover_block(fh, own, F + ((size_t)ib * 2 + d) * 18 * g.Vb + s, g.Vb);
         load6(v, in, ib, s, d, g.Vb);
         const C k = C(kappa);
 #pragma unroll
         for (int e = 0; e < 6; ++e) v[e] = rfma(-k, fh[e], v[e]);
         if constexpr (LEX) {
-            const int t = threadIdx.x >> 1;
+            const int t = pair_site(threadIdx.x);
 #pragma unroll
             for (int e = 0; e < 6; ++e) st(&tile[t * LAY_PITCH + 6 * d + e], v[e]);
             if (d == 0) lex[t] = g.blk_off[ib] + g.slot_off[s];

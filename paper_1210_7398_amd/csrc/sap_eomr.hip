@@ -69,8 +69,8 @@ __global__ void __launch_bounds__(512) k_sap_phase_eomr(GeomDev g, EomrArgs a, c
     __shared__ double red[3 * EOMR_WAVES];
     const int Vb = g.Vb, Ve = a.pstart[1];
     const int ib = a.colour * g.NBc + blockIdx.x;
-    const int d = threadIdx.x & 1;
-    const int q0 = threadIdx.x >> 1, nq = blockDim.x >> 1;
+    const int d = pair_dir(threadIdx.x);
+    const int q0 = pair_site(threadIdx.x), nq = blockDim.x >> 1;
     const float sg = d ? -1.f : 1.f;
     const float kappa = a.kappa;
     const S2 *Fk = F + ((size_t)ib * 2 + d) * 18 * Vb;
@@ -94,10 +94,8 @@ __global__ void __launch_bounds__(512) k_sap_phase_eomr(GeomDev g, EomrArgs a, c
                     gather_hop<1>(acc, g, x, U, ib, i, d, bl[1], sg);
                     gather_hop<2>(acc, g, x, U, ib, i, d, bl[2], sg);
                     gather_hop<3>(acc, g, x, U, ib, i, d, bl[3], sg);
-                    pair_reduce(acc);
                     cx<float> own[6], out[6];
-#pragma unroll
-                    for (int e = 0; e < 6; ++e) own[e] = sel(d != 0, acc[6 + e], acc[e]);
+                    pair_reduce(own, acc);
                     clover_block(out, own, Fk + i, Vb);
 #pragma unroll
                     for (int e = 0; e < 6; ++e) v[e] = v[e] + kappa * out[e];

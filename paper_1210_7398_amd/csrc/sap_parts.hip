@@ -124,8 +124,8 @@ __global__ void __launch_bounds__(512, STAGED ? 2 : 3) k_sap_phase_parts(GeomDev
         epoch = __hip_atomic_load(&a.sync[2], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     const int ib = a.colour * g.NBc + blk;
-    const int d = threadIdx.x & 1;
-    const int q0 = threadIdx.x >> 1, nq = blockDim.x >> 1;
+    const int d = pair_dir(threadIdx.x);
+    const int q0 = pair_site(threadIdx.x), nq = blockDim.x >> 1;
     const float sg = d ? -1.f : 1.f;
     const float kappa = a.kappa, omega = a.omega;
     const int *gslot = a.gslot + (size_t)part * Vp;
@@ -160,10 +160,8 @@ __global__ void __launch_bounds__(512, STAGED ? 2 : 3) k_sap_phase_parts(GeomDev
                     gather_hop<1>(acc, g, x, U, ib, s, d, bl[1], sg);
                     gather_hop<2>(acc, g, x, U, ib, s, d, bl[2], sg);
                     gather_hop<3>(acc, g, x, U, ib, s, d, bl[3], sg);
-                    pair_reduce(acc);
                     cx<float> own[6], out[6];
-#pragma unroll
-                    for (int e = 0; e < 6; ++e) own[e] = sel(d != 0, acc[6 + e], acc[e]);
+                    pair_reduce(own, acc);
                     clover_block(out, own, Fk + s, Vb);
 #pragma unroll
                     for (int e = 0; e < 6; ++e) v[e] = v[e] + kappa * out[e];
@@ -346,19 +344,18 @@ __global__ void __launch_bounds__(256) k_sap_face_2l(GeomDev g, int colour, floa
                                                      const typename Prec<P>::S2 *x,
                                                      const typename Prec<P>::S2 *__restrict__ U,
                                                      const typename Prec<P>::S2 *__restrict__ F) {
-    const long i = xcd_site_base(128) + (threadIdx.x >> 1);
-    const int d = threadIdx.x & 1;
+    const long i = xcd_site_base(128) + pair_site(threadIdx.x);
+    const int d = pair_dir(threadIdx.x);
     const long nc = (long)g.NBc * g.Vb;
     if (i >= nc) return;
     const int ib = colour * g.NBc + (int)(i / g.Vb), s = (int)(i % g.Vb);
-    int outside = 0;
+    bool outside = false;
 #pragma unroll
     for (int mu = 0; mu < 4; ++mu) {
         const unsigned w = g.nbr16[mu * g.Vb + s];
-        outside |= ((d ? (w >> 16) : w) & 0x8000u) ? 0 : 1;
+        outside |= !((d ? (w >> 16) : w) & 0x8000u);
     }
-    outside |= __builtin_amdgcn_update_dpp(0, outside, QUAD_XOR1, 0xF, 0xF, true);
-    if (!outside) return;  // both lanes of the pair leave together
+    if (!pair_any(outside)) return;  // both lanes of the pair leave together
     const float sg = d ? -1.f : 1.f;
     cx<float> acc[12];
 #pragma unroll
@@ -367,10 +364,8 @@ __global__ void __launch_bounds__(256) k_sap_face_2l(GeomDev g, int colour, floa
     gather_hop<1>(acc, g, x, U, ib, s, d, g.blk_nbr[(2 * 1 + d) * g.NB + ib], sg);
     gather_hop<2>(acc, g, x, U, ib, s, d, g.blk_nbr[(2 * 2 + d) * g.NB + ib], sg);
     gather_hop<3>(acc, g, x, U, ib, s, d, g.blk_nbr[(2 * 3 + d) * g.NB + ib], sg);
-    pair_reduce(acc);
     cx<float> own[6], out[6], v[6];
-#pragma unroll
-    for (int e = 0; e < 6; ++e) own[e] = sel(d != 0, acc[6 + e], acc[e]);
+    pair_reduce(own, acc);
     clover_block(out, own, F + ((size_t)ib * 2 + d) * 18 * g.Vb + s, g.Vb);
     load6(v, r, ib, s, d, g.Vb);
 #pragma unroll

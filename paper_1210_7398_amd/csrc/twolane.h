@@ -96,12 +96,34 @@ __device__ __forceinline__ void clover_block(cx<C> out[6], const cx<C> in[6], co
     clover_apply(out, in, F);
 }
 
-template <typename C> __device__ __forceinline__ void pair_reduce(cx<C> acc[12]) {
+// The two lanes of a site are lanes l and l + 32 of a wave: thread t of a workgroup (of whole
+// waves) takes direction pair_dir(t) of site pair_site(t), so that a wave's loads are two runs of
+// 32 sites and coalesce.  (With the two lanes of a site next to each other four neighbouring
+// lanes touched two lines, 18 cache accesses a load instead of about 5, and the address unit was
+// busy 87% of the FP16 operator's time.  A call of it at 32^3x64 took 582 us and takes 501, M_SAP
+// in FP32 at 24^3x48 4035 and 3910, on ragged BF16 blocks 2625 and 2357.)
+__device__ __forceinline__ int pair_dir(int t) { return (t >> 5) & 1; }
+__device__ __forceinline__ int pair_site(int t) { return (t >> 6) * 32 + (t & 31); }
+
+// the swap leaves lane l with both lanes' a, lane l + 32 with both lanes' b: their sum
+__device__ __forceinline__ float pair_sum(float a, float b) {
+    const auto w = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    return __uint_as_float(w[0]) + __uint_as_float(w[1]);
+}
+__device__ __forceinline__ double pair_sum(double a, double b) {
+    const auto lo = __builtin_amdgcn_permlane32_swap((unsigned)__double2loint(a), (unsigned)__double2loint(b), false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap((unsigned)__double2hiint(a), (unsigned)__double2hiint(b), false, false);
+    return __hiloint2double((int)hi[0], (int)lo[0]) + __hiloint2double((int)hi[1], (int)lo[1]);
+}
+// the lane's chiral half of the hops' sum over the pair
+template <typename C> __device__ __forceinline__ void pair_reduce(cx<C> own[6], const cx<C> acc[12]) {
 #pragma unroll
-    for (int c = 0; c < 12; ++c) {
-        acc[c].r += quad_get<QUAD_XOR1>(acc[c].r);
-        acc[c].i += quad_get<QUAD_XOR1>(acc[c].i);
-    }
+    for (int c = 0; c < 6; ++c) own[c] = {pair_sum(acc[c].r, acc[6 + c].r), pair_sum(acc[c].i, acc[6 + c].i)};
+}
+// whether p holds in either lane of the pair
+__device__ __forceinline__ bool pair_any(bool p) {
+    const auto w = __builtin_amdgcn_permlane32_swap(p, p, false, false);
+    return w[0] | w[1];
 }
 
 // the six components (spins 2d, 2d + 1) of site (ib, s) owned by lane d
@@ -197,14 +219,12 @@ __device__ __forceinline__ void block_hop_clover_impl(cx<float> out[6], cx<float
     if constexpr (STAGED && WITH_V) load6(v, vf, ib, s, d, Vb);
     if constexpr (!STAGED) link_load(u[3], U, ib, 3, sl[3], Vb);
     lds_hop<3>(acc, xs, nb.y >> 16, u[3], sg);
-    pair_reduce(acc);
     if constexpr (!STAGED) {
         load_clov(F, Fk + s, Vb);
         if constexpr (WITH_V) load6(v, vf, ib, s, d, Vb);
     }
     cx<float> own[6];
-#pragma unroll
-    for (int e = 0; e < 6; ++e) own[e] = sel(d != 0, acc[6 + e], acc[e]);
+    pair_reduce(own, acc);
     clover_apply(out, own, F);
 }
 template <typename S2>
