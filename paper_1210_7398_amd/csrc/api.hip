@@ -226,6 +226,8 @@ static void use_fp32_storage(Ctx *c, bool on) {
     c->prm.prec_inner = on ? SAPQ_FP32 : c->prec_created;
 }
 
+constexpr int N_CU = 256;  // compute units of an MI355X
+
 static size_t plan(const sapq_geom *geom, const sapq_params *prm, Ctx *c, HostTables &T, PartTables &PT, int max_lds) {
     build_tables(geom, T);
     c->geom = *geom;
@@ -271,8 +273,12 @@ static size_t plan(const sapq_geom *geom, const sapq_params *prm, Ctx *c, HostTa
             c->part_Hp = PT.Hp;
             c->part_threads = std::min(512, std::max(64, ((2 * PT.max_plane + 63) / 64) * 64));
             c->parts_lds = lds;
-            // one workgroup per CU by LDS (a gfx950 workgroup may take all of its CU's LDS)
-            c->parts_staged = (long)lds > (long)max_lds / 2;
+            c->part_max_plane = PT.max_plane;
+            // one workgroup of the phase kernel per CU: by its LDS (a gfx950 workgroup may take all of
+            // its CU's), or a whole block's by their number (of one colour)
+            long blocks = 1;
+            for (int mu = 0; mu < 4; ++mu) blocks *= geom->L[mu] / geom->block[mu];
+            c->parts_alone = (long)lds > (long)max_lds / 2 || (np == 1 && blocks / 2 <= N_CU);
             c->ssor_staged = false;
         }
     }
@@ -1138,6 +1144,7 @@ static int apply_subblock(Ctx *c, const int S[4]) {
     c->g.nplanes = T.nplanes;
     c->max_plane = T.max_plane;
     c->ssor_threads = std::min(512, ((4 * T.max_plane + 63) / 64) * 64);
+    c->part_max_plane = PT.max_plane;
     if (c->use_parts) c->part_threads = std::min(512, std::max(64, ((2 * PT.max_plane + 63) / 64) * 64));
     if (c->nn_alloc && c->have_U) {
         launch_nn_links(c);  // the layers' link table follows the slot order too

@@ -10,7 +10,7 @@
 // four backward hops.  Both run the same instructions: the projection sign is s = +1 / -1,
 // and lane 1 reads U_mu at its backward neighbour and turns it into U^+ with selects (a
 // daggered copy of the links at the site would cost a quarter more bytes per sweep).  After
-// a pair butterfly each lane owns one chiral half (spins 2d and 2d + 1), applies its 6x6
+// the pair's sum each lane owns one chiral half (spins 2d and 2d + 1), applies its 6x6
 // block of F and updates those six components.
 //
 // Parts.  The sub-block layers along t are split in halves.  Only hops in t cross between
@@ -34,10 +34,13 @@
 // halo words, the starts in registers (v_readlane), record-wise LDS, the dagger of the backward
 // links folded into signs the instructions take anyway (902 -> 760) and no relaxation
 // arithmetic at omega = 1, a launch takes 458 us instead of 533 (FP32, 6^3x12 blocks, the same
-// bits).  Measured and not kept: a site's links, or all it needs, loaded a step ahead (507 us with
+// bits), now 455: the L2 misses of its sweeps are 2.8 GB, 6.0 TB/s, what the card's memory gives, the
+// wide planes waiting on it while the narrow ones leave it idle (with every load an L2 hit it
+// would take 390).  Measured and not kept: a site's links, or all it needs, loaded a step ahead (507 us with
 // two hops' links, 10% slower than without once the waits were exact; all of it spills in FP32
 // and gains nothing in FP16).
 #include <algorithm>
+#include <type_traits>
 
 #include "twolane.h"
 
@@ -96,16 +99,24 @@ __device__ __forceinline__ float xch_wait(unsigned long long w, unsigned long lo
 // barrier for LDS traffic only: global loads (halo words) and stores stay in flight
 __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
-// STAGED: the load order of a site update (block_hop_clover_impl); the staged order holds
-// about 40 more registers, which costs nothing where a workgroup's LDS already keeps the CU
-// to one workgroup, and occupancy where several workgroups share a CU
-template <int P, int NP, bool STAGED>
-__global__ void __launch_bounds__(512, STAGED ? 2 : 3) k_sap_phase_parts(GeomDev g, PartArgs a, const typename Prec<P>::S2 *rsrc,
+// ALONE: the workgroup has a CU to itself.  A whole block (NP = 1) then takes four lanes per site on the
+// hyperplanes that its waves hold that way, and up to 12 waves: on an idle CU a step lasts as long as
+// one wave's instructions and their latency (5900 cycles at 4^4 blocks, 760 instructions), and
+// the wider planes need fewer passes.  Measured, M_SAP in FP32 unless said, two lanes -> four:
+// 4^4 blocks 813 -> 696 us (8 workgroups), 842 -> 733 (128), 963 -> 793 (256), but 1191 -> 1485
+// (384, where CUs are shared and issue slots are what is short: that kernel stays at
+// two lanes); 6^4 2115 -> 1968 (8), 5794 -> 5692 (384, alone by its LDS), in BF16 5107 -> 4627
+// (512); 6x4x10x6 in BF16 2342 -> 2011 (24).  A split block waits on its halo words, not on its own update
+// (two lanes 2773, four 2936 us at 12^3x24): it keeps two lanes, and where it is alone the
+// staged load order (block_hop_clover_impl), whose 40 registers more are free there.
+template <int P, int NP, bool ALONE>
+__global__ void __launch_bounds__(NP == 1 && ALONE ? 768 : 512, NP == 2 && ALONE ? 2 : 3) k_sap_phase_parts(GeomDev g, PartArgs a, const typename Prec<P>::S2 *rsrc,
                                                          typename Prec<P>::S2 *r, typename Prec<P>::S2 *x,
                                                          typename Prec<P>::S2 *y,
                                                          const typename Prec<P>::S2 *__restrict__ U,
                                                          const typename Prec<P>::S2 *__restrict__ F) {
     using S2 = typename Prec<P>::S2;
+    constexpr bool FOUR = NP == 1 && ALONE, STAGED = NP == 2 && ALONE;
     extern __shared__ float4 xs[];
     __shared__ unsigned sh_ticket;
     const int Vb = g.Vb, Vp = a.Vp, Hp = a.Hp;
@@ -183,6 +194,10 @@ __global__ void __launch_bounds__(512, STAGED ? 2 : 3) k_sap_phase_parts(GeomDev
     const int pl0 = a.pstart[lane], pl1 = a.pstart[lane + 1];
     const int im0 = imps[lane], im1 = imps[lane + 1];
     auto at = [](int v, int h) { return __builtin_amdgcn_readlane(v, h); };
+    const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), nwv = blockDim.x >> 6;
+    const QuadLane Q = quad_lane(lane);
+    // hyperplane h by four lanes per site
+    auto by_four = [&](int h) { return FOUR && at(pl1, h) - at(pl0, h) <= 16 * a.sweep_waves; };
     // the boundary words of a site, tagged with the sweep
     auto publish = [&](const cx<float> xn[6], int kx, int w) {
         if (kx < 0) return;
@@ -201,6 +216,14 @@ __global__ void __launch_bounds__(512, STAGED ? 2 : 3) k_sap_phase_parts(GeomDev
     uint2 nb_n = make_uint2(0u, 0u), gl_n = make_uint2(0u, 0u);
     int kx_n = -1;
     auto tables_for = [&](int h) {
+        if (by_four(h)) {
+            const int i = at(pl0, h) + 16 * wv + (lane & 15);
+            if (i < at(pl1, h)) {
+                nb_n.x = reinterpret_cast<const unsigned *>(pnb)[4 * i + 2 * Q.d + Q.m];
+                gl_n.x = reinterpret_cast<const unsigned *>(gnb)[2 * i + Q.m];
+            }
+            return;
+        }
         const int i = at(pl0, h) + q0;
         if (i < at(pl1, h)) {
             nb_n = pnb[2 * i + d];
@@ -209,7 +232,6 @@ __global__ void __launch_bounds__(512, STAGED ? 2 : 3) k_sap_phase_parts(GeomDev
         }
     };
     tables_for(0);
-    const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), nwv = blockDim.x >> 6;
     // The halo words of `n` slots (slot index k(e)) from sweep slot `src`, checked against `tag`, into
     // LDS, one slot per lane: all 24 loads in flight, then the waits.
     auto import_words = [&](int n, auto k_of, int src, unsigned tag) {
@@ -243,25 +265,41 @@ __global__ void __launch_bounds__(512, STAGED ? 2 : 3) k_sap_phase_parts(GeomDev
                 // the site's last update, so with omega = 1 (no (1 - omega) x term) the update
                 // would give the same value bit for bit: it is skipped and only the boundary
                 // words are published again under the new sweep's tag.
+                // the new value of N components of site i from component c0 on, from F of its hops and its v
+                auto relax = [&](auto n, cx<float> *xn, const cx<float> *out, const cx<float> *v, int i, int c0) {
+                    constexpr int N = decltype(n)::value;
+#pragma unroll
+                    for (int e = 0; e < N; ++e) xn[e] = v[e] + kappa * out[e];
+                    if (omega != 1.f) {
+                        const float2 *xf = reinterpret_cast<const float2 *>(xs) + 12 * i + c0;
+#pragma unroll
+                        for (int e = 0; e < N; ++e) {
+                            const float2 ov = xf[e];
+                            xn[e] = {(1.f - omega) * ov.x + omega * xn[e].r, (1.f - omega) * ov.y + omega * xn[e].i};
+                        }
+                    }
+                };
                 if (omega == 1.f && w > 0 && pi == 0) {
                     for (int i = i0; NP == 2 && i < i_hi; i += ns) {
                         cx<float> xn[6];
                         lds_get6(xn, xs, d, i);
                         publish(xn, i == i0 ? kx0 : expi[i], w);
                     }
+                } else if (by_four(h)) {
+                    const int i = i_lo + 16 * wv + (lane & 15), c0 = 6 * Q.d + 3 * Q.m;
+                    if (i < i_hi) {
+                        cx<float> out[3], v[3], xn[3];
+                        quad_hop_clover_v(out, v, vb, xs, nb0.x, gl0.x, U, F, ib, i + shift, Q, Vb);
+                        relax(std::integral_constant<int, 3>(), xn, out, v, i, c0);
+                        float2 *xf = reinterpret_cast<float2 *>(xs) + 12 * i + c0;
+#pragma unroll
+                        for (int e = 0; e < 3; ++e) xf[e] = make_float2(xn[e].r, xn[e].i);
+                    }
                 } else {
                     auto update = [&](int i, uint2 nb, uint2 gl, int kx) {
                         cx<float> out[6], v[6], xn[6];
                         block_hop_clover_v<STAGED>(out, v, vb, xs, nb, gl, U, Fk, ib, i + shift, d, Vb, sg);
-#pragma unroll
-                        for (int e = 0; e < 6; ++e) xn[e] = v[e] + kappa * out[e];
-                        if (omega != 1.f) {
-                            cx<float> ov[6];
-                            lds_get6(ov, xs, d, i);
-#pragma unroll
-                            for (int e = 0; e < 6; ++e)
-                                xn[e] = {(1.f - omega) * ov[e].r + omega * xn[e].r, (1.f - omega) * ov[e].i + omega * xn[e].i};
-                        }
+                        relax(std::integral_constant<int, 6>(), xn, out, v, i, 6 * d);
                         lds_put6(xs, d, i, xn);
                         if constexpr (NP == 2) publish(xn, kx, w);
                     };
@@ -382,13 +420,13 @@ void launch_sap_face_2l(Ctx *c, int colour, void *r, const void *x) {
                                          (const typename Prec<P_>::S2 *)c->Fin)));
 }
 
-template <int P> static void *parts_kernel(int np, bool staged) {
-    return np == 2 ? (staged ? (void *)k_sap_phase_parts<P, 2, true> : (void *)k_sap_phase_parts<P, 2, false>)
-                   : (staged ? (void *)k_sap_phase_parts<P, 1, true> : (void *)k_sap_phase_parts<P, 1, false>);
+template <int P> static void *parts_kernel(int np, bool alone) {
+    return np == 2 ? (alone ? (void *)k_sap_phase_parts<P, 2, true> : (void *)k_sap_phase_parts<P, 2, false>)
+                   : (alone ? (void *)k_sap_phase_parts<P, 1, true> : (void *)k_sap_phase_parts<P, 1, false>);
 }
 static void *parts_kernel(const Ctx *c) {
     void *fn = nullptr;
-    INNER_SWITCH(c->prm.prec_inner, fn = parts_kernel<P_>(c->sap_np, c->parts_staged));
+    INNER_SWITCH(c->prm.prec_inner, fn = parts_kernel<P_>(c->sap_np, c->parts_alone));
     return fn;
 }
 
@@ -416,8 +454,10 @@ void launch_sap_phase_parts(Ctx *c, int colour, int gather, int first, int ssor_
     a.spin_limit = c->halo_spin_limit;
     a.wait_xor = c->halo_wait_xor;
     // two lanes per site of the widest hyperplane, and for a split block a wave for the halo words
-    // (the last one does both where the sweeps take all eight)
-    a.sweep_waves = c->part_threads / 64;
+    // (the last one does both where the sweeps take all eight); with four lanes per site up to the 12 waves
+    // that the kernel's registers allow
+    const bool four = c->sap_np == 1 && c->parts_alone;
+    a.sweep_waves = four ? std::min(12, (c->part_max_plane + 15) / 16) : c->part_threads / 64;
     const int waves = c->sap_np == 2 ? std::min(8, a.sweep_waves + 1) : a.sweep_waves;
     a.halo_wave = waves - 1;
     const dim3 grid(c->g.NBc * c->sap_np), block(64 * waves);

@@ -249,9 +249,9 @@ struct Ctx {
     size_t staged_bytes;
     // two-lanes-per-site phase kernel, the block split along t into sap_np workgroups
     bool use_parts = false;
-    int sap_np = 1, part_Vp = 0, part_Hp = 0, part_threads = 512;
+    int sap_np = 1, part_Vp = 0, part_Hp = 0, part_max_plane = 0, part_threads = 512;
     size_t parts_lds = 0;
-    bool parts_staged = false;  // phase kernel in the staged load order (one workgroup per CU by LDS)
+    bool parts_alone = false;  // a workgroup of the two-lane phase kernel has a CU to itself
     int *part_gslot, *part_pstart, *part_exp, *part_imp, *part_imps;
     uint2 *part_nb, *part_gnb;
     uint4 *eo_nb;  // tables of the one-lane even-odd phase kernel (csrc/sapeo.h)

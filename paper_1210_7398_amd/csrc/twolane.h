@@ -120,6 +120,11 @@ template <typename C> __device__ __forceinline__ void pair_reduce(cx<C> own[6], 
 #pragma unroll
     for (int c = 0; c < 6; ++c) own[c] = {pair_sum(acc[c].r, acc[6 + c].r), pair_sum(acc[c].i, acc[6 + c].i)};
 }
+// the row swap leaves a's sum over lanes l and l + 16 in the even rows of 16 lanes, b's in the odd ones
+__device__ __forceinline__ float row_sum(float a, float b) {
+    const auto w = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    return __uint_as_float(w[0]) + __uint_as_float(w[1]);
+}
 // whether p holds in either lane of the pair
 __device__ __forceinline__ bool pair_any(bool p) {
     const auto w = __builtin_amdgcn_permlane32_swap(p, p, false, false);
@@ -246,6 +251,122 @@ __device__ __forceinline__ void block_hop_clover_v(cx<float> out[6], cx<float> v
                                                    uint2 nb, uint2 gl, const S2 *U, const S2 *Fk, int ib, int s,
                                                    int d, int Vb, float sg) {
     block_hop_clover_impl<true, STAGED>(out, v, vf, xs, nb, gl, U, Fk, ib, s, d, Vb, sg);
+}
+
+// ================================================================ four lanes per site
+// The same update by four lanes: rows of 16 lanes (d, m) = (0, 0), (0, 1), (1, 0), (1, 1) of a wave share 16
+// sites, lane m taking the hops mu = 2m and 2m + 1 of direction d and then spin 2d + m of the
+// result.  Directions x and z (J = 0), and y and t (J = 1), have the same spin structure up to
+// the order of the lower spins, which lane m = 1 reads as (2, 3) and lane m = 0 as (3, 2), and the sign
+// t = +1 / -1 of one of the two half spinors.  acc: spins 0, 1 and the lower spins in that order.
+struct QuadLane {
+    int d, m;
+    float s, t, st;  // s = +1 / -1: direction, t: row pair, their product
+};
+__device__ __forceinline__ QuadLane quad_lane(int lane) {
+    QuadLane q;
+    q.d = lane >> 5;
+    q.m = (lane >> 4) & 1;
+    q.s = q.d ? -1.f : 1.f;
+    q.t = q.m ? -1.f : 1.f;
+    q.st = q.s * q.t;
+    return q;
+}
+template <int J>
+__device__ __forceinline__ void quad_hop(cx<float> acc[12], const float4 *xs, unsigned slot, cx<float> u[9], const QuadLane &Q) {
+    const float s = Q.s, t = Q.t, st = Q.st;
+    cx<float> p[6], q0[3], q1[3], h0[3], h1[3], g0[3], g1[3];
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+        const float4 f = xs[6 * slot + q];
+        p[2 * q] = {f.x, f.y};
+        p[2 * q + 1] = {f.z, f.w};
+    }
+    const float2 *lo = reinterpret_cast<const float2 *>(xs) + 12 * slot;
+    const int o0 = Q.m ? 6 : 9;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        const float2 f0 = lo[o0 + a], f1 = lo[15 - o0 + a];
+        q0[a] = {f0.x, f0.y};
+        q1[a] = {f1.x, f1.y};
+    }
+    link_rebuild(u);
+    link_swap(u, Q.d != 0);
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        const cx<float> p0 = p[a], p1 = p[3 + a];
+        if (J == 0) {
+            h0[a] = {fmx(-s, q0[a].i, p0.r), fmx(s, p0.i, q0[a].r)};
+            h1[a] = {fmx(-st, q1[a].i, p1.r), fmx(s, p1.i, t * q1[a].r)};
+        } else {
+            h0[a] = {fmx(st, q0[a].r, p0.r), fmx(s, p0.i, t * q0[a].i)};
+            h1[a] = {fmx(-s, q1[a].r, p1.r), fmx(s, p1.i, -q1[a].i)};
+        }
+    }
+    su3_mul(g0, u, h0, false);
+    su3_mul(g1, u, h1, false);
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        if (J == 0) {
+            acc[a] = {g0[a].r, s * g0[a].i};
+            acc[3 + a] = {g1[a].r, s * g1[a].i};
+            acc[6 + a] = {g0[a].i, -s * g0[a].r};
+            acc[9 + a] = {t * g1[a].i, -st * g1[a].r};
+        } else {
+            acc[a] = {acc[a].r + g0[a].r, fmx(s, g0[a].i, acc[a].i)};
+            acc[3 + a] = {acc[3 + a].r + g1[a].r, fmx(s, g1[a].i, acc[3 + a].i)};
+            acc[6 + a] = {fmx(st, g0[a].r, acc[6 + a].r), fmx(t, g0[a].i, acc[6 + a].i)};
+            acc[9 + a] = {fmx(-s, g1[a].r, acc[9 + a].r), acc[9 + a].i - g1[a].i};
+        }
+    }
+}
+
+// out = spin 2d + m of F sum_{m in block} H_nm x_m at site (ib, s), v = that spin of vf.  nb, gl: the lane's two
+// neighbour slots in LDS and backward neighbours' block slots (16 bits each).  Row m of the chiral block is [A B] or [B^+ C], so lane m = 1 reads B transposed
+// and takes its conjugate.
+template <typename S2>
+__device__ __forceinline__ void quad_hop_clover_v(cx<float> out[3], cx<float> v[3], const S2 *vf, const float4 *xs,
+                                                  unsigned nb, unsigned gl, const S2 *U, const S2 *F, int ib, int s,
+                                                  const QuadLane &Q, int Vb) {
+    const S2 *Ub = U + (size_t)ib * 24 * Vb, *Fb = F + (size_t)ib * 36 * Vb, *vb = vf + (size_t)ib * 12 * Vb;
+    cx<float> u0[9], u1[9], acc[12];
+    const int l0 = 12 * Q.m * Vb + (Q.d ? (int)(gl & 0xffffu) : s), l1 = (12 * Q.m + 6) * Vb + (Q.d ? (int)(gl >> 16) : s);
+#pragma unroll
+    for (int e = 0; e < 6; ++e) u0[e] = ld(Ub + (l0 + e * Vb));
+#pragma unroll
+    for (int e = 0; e < 6; ++e) u1[e] = ld(Ub + (l1 + e * Vb));
+    quad_hop<0>(acc, xs, nb & 0xffffu, u0, Q);
+    const int f0 = 18 * Q.d * Vb + s;
+    const cx<float> d23 = ld(Fb + (f0 + Vb)), dd = ld(Fb + (f0 + 2 * Q.m * Vb));
+    cx<float> T[3], B[9];
+#pragma unroll
+    for (int e = 0; e < 3; ++e) T[e] = ld(Fb + (f0 + (3 + 3 * Q.m + e) * Vb));
+    const int sa = Q.m ? Vb : 3 * Vb, sb = Q.m ? 3 * Vb : Vb, f9 = f0 + 9 * Vb;
+#pragma unroll
+    for (int a = 0; a < 3; ++a)
+#pragma unroll
+        for (int b = 0; b < 3; ++b) B[3 * a + b] = ld(Fb + (f9 + a * sa + b * sb));
+    const int v0 = (6 * Q.d + 3 * Q.m) * Vb + s;
+#pragma unroll
+    for (int e = 0; e < 3; ++e) v[e] = ld(vb + (v0 + e * Vb));
+    quad_hop<1>(acc, xs, nb >> 16, u1, Q);
+    cx<float> half[6], x[3], y[3];  // x: the lane's spin of the sum, y: the other one of its chiral half
+    pair_reduce(half, acc);
+    const bool swap = Q.d && !Q.m;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        const cx<float> ev = sel(swap, half[3 + a], half[a]), od = sel(swap, half[a], half[3 + a]);
+        x[a] = {row_sum(ev.r, od.r), row_sum(ev.i, od.i)};
+        y[a] = {row_sum(od.r, ev.r), row_sum(od.i, ev.i)};
+    }
+    const float e0 = Q.m ? d23.i : dd.r, e1 = Q.m ? dd.r : dd.i, e2 = Q.m ? dd.i : d23.r;
+    out[0] = cfmac(T[1], x[2], cfmac(T[0], x[1], e0 * x[0]));
+    out[1] = cfmac(T[2], x[2], cfma(T[0], x[0], e1 * x[1]));
+    out[2] = cfma(T[2], x[1], cfma(T[1], x[0], e2 * x[2]));
+#pragma unroll
+    for (int a = 0; a < 3; ++a)
+#pragma unroll
+        for (int b = 0; b < 3; ++b) out[a] = cfma(cx<float>{B[3 * a + b].r, Q.t * B[3 * a + b].i}, y[b], out[a]);
 }
 
 // one hop leaving the block (neighbour in another block, from the global iterate x)
