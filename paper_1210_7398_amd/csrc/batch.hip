@@ -13,6 +13,7 @@
 #include <cstring>
 #include <mutex>
 #include <string>
+#include <type_traits>
 #include <vector>
 
 #include "sapeo.h"
@@ -21,9 +22,9 @@
 namespace sapq {
 
 // inner vector slots (storage precision), rhs-major: slot base + k * nvec
-enum { IV_R, IV_RT, IV_P, IV_V, IV_S, IV_T, IV_E, IV_PH, IV_SH, IV_SAPR, IV_SAPX, IV_RIN, IV_Z, IV_RP, NIV };
+enum { IV_R, IV_RT, IV_P, IV_V, IV_S, IV_T, IV_E, IV_PH, IV_SH, IV_SAPR, IV_SAPX, IV_Z, IV_RP, NIV };
 // outer vector slots (FP64)
-enum { DV_B, DV_X, DV_R, DV_T, NDV };
+enum { DV_B, DV_X, DV_R, NDV };
 
 constexpr int MAX_FIELDS = 16;
 
@@ -469,32 +470,42 @@ __global__ void __launch_bounds__(256) k_bsap_face_2l(const BatchDev *__restrict
     store6(r, ib, s, d, g.Vb, v);
 }
 
-// out = D in in FP64 for every field and right-hand side (outer slots)
-__global__ void __launch_bounds__(256) k_bdslash64(const BatchDev *__restrict__ Bd, int s_out, int s_in) {
-    using C = double;
+// r = b - D x in FP64 for every field and right-hand side.  Two lanes per site as in k_dslash.  Bound by
+// memory: a site's links and clover rows (960 bytes) serve all its field's sources, so the
+// sources of a tile of sites are consecutive workgroups of one XCD and share them in its L2.  At
+// 6 sources of 16^3x32 and 6 of 8^3x16 it takes 233 us, against 388 with four lanes per site, sources
+// apart in the grid and the difference in a kernel of its own.
+constexpr int BRES_SITES = 64;
+static unsigned bresid_grid(long V, int nrhs) {  // workgroups for one field
+    return (unsigned)((V + BRES_SITES * N_XCD - 1) / (BRES_SITES * N_XCD)) * N_XCD * nrhs;
+}
+__global__ void __launch_bounds__(2 * BRES_SITES, 2) k_bresid(const BatchDev *__restrict__ Bd) {
     const BatchDev &B = *Bd;
-    const int fi = blockIdx.y, k = blockIdx.z;
-    if (fi >= B.nf) return;
-    const BField &F = B.f[fi];
-    if (k >= F.nrhs) return;
+    const BField &F = B.f[blockIdx.y];
     const GeomDev &g = F.g;
-    const long gt = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    const long i = gt >> 2;
-    const int j = (int)(gt & 3);
+    const int tiles = (int)((g.V + BRES_SITES * N_XCD - 1) / (BRES_SITES * N_XCD));  // of one XCD
+    const int w = blockIdx.x / N_XCD, tile = w / F.nrhs, k = w - tile * F.nrhs;
+    if (tile >= tiles) return;
+    const long i = ((long)(blockIdx.x % N_XCD) * tiles + tile) * BRES_SITES + pair_site(threadIdx.x);
     if (i >= g.V) return;
-    const int ib = (int)(i / g.Vb), s = (int)(i - (long)ib * g.Vb);
+    const int d = pair_dir(threadIdx.x);
+    const int bl = (int)(i / g.Vb), s = (int)(i - (long)bl * g.Vb), ib = g.lex_blk[bl];
     const size_t ko = (size_t)k * F.nvec;
-    const double2 *in = F.dv[s_in] + ko;
-    double2 *out = F.dv[s_out] + ko;
-    const LaneNbr n = lane_nbr(g.nbr16[j * g.Vb + s], ib, g.blk_nbr[(2 * j) * g.NB + ib],
-                               g.blk_nbr[(2 * j + 1) * g.NB + ib], g.bc[j]);
-    cx<C> h[12], fh[3], v[3];
-    quad_hop_sum<HOP_ALL, false>(h, g, ib, s, j, n, F.U64, FieldSrc<double2, C>{in});
-    lane_clover(fh, h, F.F64, g, ib, s, j);
-    load_spin(v, in, g, ib, s, j);
+    const double2 *x = F.dv[DV_X] + ko, *U = F.U64;
+    const double sg = d ? -1.0 : 1.0, kappa = (double)F.kappa;
+    cx<double> acc[12];
+    hop_any<0>(acc, g, x, U, ib, s, d, sg);
+    hop_any<1>(acc, g, x, U, ib, s, d, sg);
+    hop_any<2>(acc, g, x, U, ib, s, d, sg);
+    hop_any<3>(acc, g, x, U, ib, s, d, sg);
+    cx<double> own[6], fh[6], v[6], b[6];
+    pair_reduce(own, acc);
+    clover_block(fh, own, F.F64 + ((size_t)ib * 2 + d) * 18 * g.Vb + s, g.Vb);
+    load6(v, x, ib, s, d, g.Vb);
+    load6(b, F.dv[DV_B] + ko, ib, s, d, g.Vb);
 #pragma unroll
-    for (int c = 0; c < 3; ++c) v[c] = v[c] - (double)F.kappa * fh[c];
-    store_spin(out, g, ib, s, j, v);
+    for (int e = 0; e < 6; ++e) b[e] = b[e] - rfma(-kappa, fh[e], v[e]);
+    store6(F.dv[DV_R] + ko, ib, s, d, g.Vb, b);
 }
 
 // ---------------------------------------------------------------- batched vector updates
@@ -577,22 +588,11 @@ __global__ void k_bupdate_e(const BatchDev *__restrict__ Bd, const BState *__res
         st(e + i, ld(e + i) + cmul(a, ld(ph + i)) + cmul(o, ld(sh + i)));
 }
 
-template <int P>
-__global__ void k_bzero(const BatchDev *__restrict__ Bd, int slot) {
-    using C = typename Prec<P>::C;
-    using S2 = typename Prec<P>::S2;
-    const BatchDev &B = *Bd;
-    const int fi = blockIdx.y;
-    if (fi >= B.nf) return;
-    const BField &F = B.f[fi];
-    S2 *z = (S2 *)F.iv[slot];
-    const size_t n = F.nvec * F.nrhs;
-    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x)
-        st(z + i, cxz<C>());
-}
-
-// dot products <a_q, b_q> (q < nd) per right-hand side: partial sums per workgroup
-constexpr int BDOT_BLOCKS = 64;
+// dot products <a_q, b_q> (q < nd) per right-hand side: partial sums per workgroup, in a fixed order.
+// With one
+// element's loads in flight per thread it ran at their latency (54 us at 6 sources of 16^3x32 and
+// 6 of 8^3x16 in FP16); with BDOT_AHEAD elements' 26.
+constexpr int BDOT_BLOCKS = 64, BDOT_AHEAD = 8;
 template <int P, bool OUTER>
 __global__ void __launch_bounds__(256) k_bdots(const BatchDev *__restrict__ Bd, int nd, int a0, int b0, int a1, int b1,
                                                double *__restrict__ partials /* [rhs][BDOT_BLOCKS][4] */) {
@@ -609,16 +609,28 @@ __global__ void __launch_bounds__(256) k_bdots(const BatchDev *__restrict__ Bd, 
     const S2 *A1 = (const S2 *)(OUTER ? (const void *)F.dv[a1] : F.iv[a1]) + ko;
     const S2 *B1 = (const S2 *)(OUTER ? (const void *)F.dv[b1] : F.iv[b1]) + ko;
     double acc[4] = {0, 0, 0, 0};
-    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < F.nvec; i += (size_t)gridDim.x * blockDim.x) {
-        auto x = ld(A0 + i), y = ld(B0 + i);
-        acc[0] += (double)x.r * y.r + (double)x.i * y.i;
-        acc[1] += (double)x.r * y.i - (double)x.i * y.r;
-        if (nd > 1) {
-            auto u = ld(A1 + i), w = ld(B1 + i);
-            acc[2] += (double)u.r * w.r + (double)u.i * w.i;
-            acc[3] += (double)u.r * w.i - (double)u.i * w.r;
-        }
-    }
+    const size_t st = (size_t)gridDim.x * blockDim.x;
+    size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+    // the terms of BDOT_AHEAD elements, added in the order of the elements
+    auto add = [&](auto n) {
+        constexpr int N = decltype(n)::value;
+        auto dot = [&](const S2 *A, const S2 *Bv, int q) {
+            S2 x[N], y[N];
+#pragma unroll
+            for (int t = 0; t < N; ++t) x[t] = A[i + t * st], y[t] = Bv[i + t * st];
+#pragma unroll
+            for (int t = 0; t < N; ++t) {
+                const auto a = ld(&x[t]), b = ld(&y[t]);
+                acc[2 * q] += (double)a.r * b.r + (double)a.i * b.i;
+                acc[2 * q + 1] += (double)a.r * b.i - (double)a.i * b.r;
+            }
+        };
+        dot(A0, B0, 0);
+        if (nd > 1) dot(A1, B1, 1);
+        i += N * st;
+    };
+    while (i + (BDOT_AHEAD - 1) * st < F.nvec) add(std::integral_constant<int, BDOT_AHEAD>());
+    while (i < F.nvec) add(std::integral_constant<int, 1>());
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
@@ -760,7 +772,9 @@ __global__ void k_bouter(const BatchDev *__restrict__ Bd, const double *__restri
     S.its = 0;
 }
 
-// inner storage <-> FP64 outer, with a per-right-hand-side scale from the outer norms
+// A new inner solve in inner storage: R = RT = the scaled FP64 residual (a finished source, scale 0,
+// keeps its RT), P = V = E = 0, one pass for what took a conversion, two copies and three
+// clears (142 -> 60 us at the sizes above).
 template <int P>
 __global__ void k_bconvert_in(const BatchDev *__restrict__ Bd, const BOuter *__restrict__ os) {
     using C = typename Prec<P>::C;
@@ -771,13 +785,19 @@ __global__ void k_bconvert_in(const BatchDev *__restrict__ Bd, const BOuter *__r
     const BField &F = B.f[fi];
     if (k >= F.nrhs) return;
     const double sc = os[F.rhs0 + k].scale;
-    if (sc == 0) return;
     const size_t ko = (size_t)k * F.nvec;
-    S2 *d = (S2 *)F.iv[IV_RIN] + ko;
+    S2 *r = (S2 *)F.iv[IV_R] + ko, *rt = (S2 *)F.iv[IV_RT] + ko, *p = (S2 *)F.iv[IV_P] + ko, *v = (S2 *)F.iv[IV_V] + ko,
+       *e = (S2 *)F.iv[IV_E] + ko;
     const double2 *s = F.dv[DV_R] + ko;
     for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < F.nvec; i += (size_t)gridDim.x * blockDim.x) {
-        double2 v = s[i];
-        st(d + i, cx<C>{C(v.x * sc), C(v.y * sc)});
+        if (sc != 0) {
+            const double2 t = s[i];
+            st(rt + i, cx<C>{C(t.x * sc), C(t.y * sc)});
+        }
+        r[i] = rt[i];
+        st(p + i, cxz<C>());
+        st(v + i, cxz<C>());
+        st(e + i, cxz<C>());
     }
 }
 
@@ -804,38 +824,10 @@ __global__ void k_bconvert_out(const BatchDev *__restrict__ Bd, const BOuter *__
     }
 }
 
-// r = b - t (FP64)
-__global__ void k_bresid(const BatchDev *__restrict__ Bd) {
-    const BatchDev &B = *Bd;
-    const int fi = blockIdx.y, k = blockIdx.z;
-    if (fi >= B.nf) return;
-    const BField &F = B.f[fi];
-    if (k >= F.nrhs) return;
-    const size_t ko = (size_t)k * F.nvec;
-    const double2 *b = F.dv[DV_B] + ko, *t = F.dv[DV_T] + ko;
-    double2 *r = F.dv[DV_R] + ko;
-    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < F.nvec; i += (size_t)gridDim.x * blockDim.x)
-        r[i] = make_double2(b[i].x - t[i].x, b[i].y - t[i].y);
-}
-
-template <int P>
-__global__ void k_bcopy(const BatchDev *__restrict__ Bd, int s_d, int s_s) {
-    using S2 = typename Prec<P>::S2;
-    const BatchDev &B = *Bd;
-    const int fi = blockIdx.y;
-    if (fi >= B.nf) return;
-    const BField &F = B.f[fi];
-    S2 *d = (S2 *)F.iv[s_d];
-    const S2 *s = (const S2 *)F.iv[s_s];
-    const size_t n = F.nvec * F.nrhs;
-    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) d[i] = s[i];
-}
-
 // ---------------------------------------------------------------- host driver
 struct Batch {
     std::vector<Ctx *> ctx;
     int nf = 0, total = 0, max_rhs = 0;
-    long max_V = 0;
     int prec = SAPQ_FP32, NR = 1;
     bool two_lane = false;  // k_bsap_phase_2l (else the four-lane k_bsap_phase)
     bool eo = false;        // k_bsap_phase_eo: every context runs the one-lane even-odd kernel, one source per workgroup
@@ -897,7 +889,6 @@ static int setup_batch(Batch &B, sapq_ctx *const *ctxs, int nctx, const int *nrh
         if (!c->have_U || !c->have_F) { why = "fields must be loaded in every context"; return SAPQ_ESTATE; }
         if (c->prm.flags & SAPQ_FLAG_EOMR) { why = "the batched solver runs the SSOR block inverses only"; return SAPQ_EINVAL; }
         B.max_rhs = std::max(B.max_rhs, nrhs[f]);
-        B.max_V = std::max(B.max_V, c->V);
     }
     Ctx *c0 = B.ctx[0];
     B.prec = c0->prm.prec_inner;
@@ -1142,20 +1133,15 @@ static std::vector<unsigned long long> batch_key(const Batch &B, const void *are
 // inner BiCGStab on the scaled residual for those.
 static void outer_step(Batch &B, double tol, double tol_in, int maxit_in) {
     dim3 vg = vgrid(B);
-    dim3 dg((unsigned)((4 * B.max_V + 255) / 256), (unsigned)B.nf, (unsigned)B.max_rhs);
+    unsigned rg = 0;
+    for (int f = 0; f < B.nf; ++f) rg = std::max(rg, bresid_grid(B.host.f[f].g.V, B.host.f[f].nrhs));
     dim3 bd(BDOT_BLOCKS, (unsigned)B.nf, (unsigned)B.max_rhs);
     BPREC(B.prec, (k_bconvert_out<P_><<<vg, 256, 0, B.stream>>>(B.dev, B.os, B.st)));
-    k_bdslash64<<<dg, 256, 0, B.stream>>>(B.dev, DV_T, DV_X);
-    k_bresid<<<vg, 256, 0, B.stream>>>(B.dev);
+    k_bresid<<<dim3(rg, (unsigned)B.nf), 2 * BRES_SITES, 0, B.stream>>>(B.dev);
     k_bdots<SAPQ_FP64, true><<<bd, 256, 0, B.stream>>>(B.dev, 1, DV_R, DV_R, DV_R, DV_R, B.partials);
     k_bouter<<<(B.total + 63) / 64, 64, 0, B.stream>>>(B.dev, B.partials, B.os, B.st, tol);
     bcount(B);
     BPREC(B.prec, (k_bconvert_in<P_><<<vg, 256, 0, B.stream>>>(B.dev, B.os)));
-    BPREC(B.prec, (k_bcopy<P_><<<dim3(256, B.nf), 256, 0, B.stream>>>(B.dev, IV_R, IV_RIN)));
-    BPREC(B.prec, (k_bcopy<P_><<<dim3(256, B.nf), 256, 0, B.stream>>>(B.dev, IV_RT, IV_RIN)));
-    BPREC(B.prec, (k_bzero<P_><<<dim3(256, B.nf), 256, 0, B.stream>>>(B.dev, IV_P)));
-    BPREC(B.prec, (k_bzero<P_><<<dim3(256, B.nf), 256, 0, B.stream>>>(B.dev, IV_V)));
-    BPREC(B.prec, (k_bzero<P_><<<dim3(256, B.nf), 256, 0, B.stream>>>(B.dev, IV_E)));
     bdots(B, 2, IV_RT, IV_R, IV_R, IV_R);
     bscalar(B, SC_INIT, tol_in, maxit_in);
 }

@@ -90,7 +90,7 @@ struct BlockSrc {  // the float2 [12][Vb] SSOR iterate of the current block (LDS
     }
 };
 
-enum { HOP_ALL = 0, HOP_IN = 1, HOP_OUT = 2 };
+enum { HOP_IN, HOP_OUT };  // hops inside the block, hops leaving it
 
 // value of the lane (lane ^ 1) or (lane ^ 2) of the same quad, by DPP quad permutes
 template <int CTRL> __device__ __forceinline__ float quad_get(float v) {
@@ -161,8 +161,8 @@ template <int MODE, typename C, typename Src>
 __device__ __forceinline__ void quad_hop_apply(cx<C> acc[12], const GeomDev &g, int j, const LaneNbr &n,
                                                const LaneLinks<C> &l, const Src &src) {
     const LaneDir<C> d = lane_dir<C>(j);
-    const bool use_f = MODE == HOP_ALL || (MODE == HOP_IN ? n.in_f : !n.in_f);
-    const bool use_b = MODE == HOP_ALL || (MODE == HOP_IN ? n.in_b : !n.in_b);
+    const bool use_f = MODE == HOP_IN ? n.in_f : !n.in_f;
+    const bool use_b = MODE == HOP_IN ? n.in_b : !n.in_b;
 #pragma unroll
     for (int c = 0; c < 12; ++c) acc[c] = cxz<C>();
     {
