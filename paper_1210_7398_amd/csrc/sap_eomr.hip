@@ -30,8 +30,8 @@ struct EomrArgs {
     const int *pstart;  // [0] = 0, [1] = Ve, [2] = Vb
 };
 
-constexpr int EOMR_MAXK = 4;   // sites of one parity per lane pair (the kernel's K, at most)
-constexpr int EOMR_WAVES = 8;  // at most 512 threads
+constexpr int EOMR_MAX_SITES = 1024;  // of one parity in a block
+constexpr int EOMR_WAVES = 12;        // at most 768 threads
 
 // sums of a, b, c over the workgroup, the same values (same order) in every thread
 __device__ __forceinline__ void block_sum3(double &a, double &b, double &c, double *red) {
@@ -57,9 +57,15 @@ __device__ __forceinline__ void block_sum3(double &a, double &b, double &c, doub
 }
 
 // K: sites of one parity per lane pair, the smallest that covers the block (x_e and p of
-// those sites stay in registers across the steps)
+// those sites stay in registers across the steps).  What bounds it: the latency of a site's
+// loads and instructions, with the waves that the registers of an LDS-filled CU allow, and at
+// 24^3x48 memory.  Left alone the compiler keeps the tables and addresses of all K sites across
+// the steps (39 registers spilled at K = 3 and two waves a SIMD); with the site index opaque and the
+// sites kept apart, K = 2 fits three waves a SIMD.  M_SAP with 6^4 blocks at 24^3x48: FP32
+// 3640 -> 3279 us (eight waves without the spills 3345), FP16 2527 (eight waves) -> 2393; 4x6x4x8
+// blocks at 16^2x24x32, FP32, 1537 (eight waves) -> 1252.
 template <int P, int K>
-__global__ void __launch_bounds__(512) k_sap_phase_eomr(GeomDev g, EomrArgs a, const typename Prec<P>::S2 *rsrc,
+__global__ void __launch_bounds__(64 * EOMR_WAVES, 3) k_sap_phase_eomr(GeomDev g, EomrArgs a, const typename Prec<P>::S2 *rsrc,
                                                         typename Prec<P>::S2 *r, typename Prec<P>::S2 *x,
                                                         typename Prec<P>::S2 *y,
                                                         const typename Prec<P>::S2 *__restrict__ U,
@@ -116,6 +122,7 @@ __global__ void __launch_bounds__(512) k_sap_phase_eomr(GeomDev g, EomrArgs a, c
     cx<float> xe[K][6];
 #pragma unroll
     for (int k = 0; k < K; ++k) {
+        __builtin_amdgcn_sched_barrier(0);
         const int i = q0 + k * nq;
 #pragma unroll
         for (int e = 0; e < 6; ++e) xe[k][e] = cxz<float>();
@@ -146,7 +153,9 @@ __global__ void __launch_bounds__(512) k_sap_phase_eomr(GeomDev g, EomrArgs a, c
         double pr = 0.0, pi = 0.0, pp = 0.0;
 #pragma unroll
         for (int k = 0; k < K; ++k) {
-            const int i = q0 + k * nq;
+            __builtin_amdgcn_sched_barrier(0);
+            int i = q0 + k * nq;
+            asm volatile("" : "+v"(i));
 #pragma unroll
             for (int e = 0; e < 6; ++e) pe[k][e] = cxz<float>();
             if (i < Ve) {
@@ -168,6 +177,7 @@ __global__ void __launch_bounds__(512) k_sap_phase_eomr(GeomDev g, EomrArgs a, c
         // (c) x_e += alpha r_e,  r_e -= alpha p  (the new r_e onto the even slots)
 #pragma unroll
         for (int k = 0; k < K; ++k) {
+            __builtin_amdgcn_sched_barrier(0);
             const int i = q0 + k * nq;
             if (i < Ve) {
                 cx<float> rv[6];
@@ -186,6 +196,7 @@ __global__ void __launch_bounds__(512) k_sap_phase_eomr(GeomDev g, EomrArgs a, c
     // 4. x_e onto the even slots, then x_o = v_o + K_oe x_e onto the odd ones
 #pragma unroll
     for (int k = 0; k < K; ++k) {
+        __builtin_amdgcn_sched_barrier(0);
         const int i = q0 + k * nq;
         if (i < Ve) lds_put6(xs, d, i, xe[k]);
     }
@@ -230,10 +241,15 @@ static int eomr_vb(const Ctx *c) {
     return c->geom.block[0] * c->geom.block[1] * c->geom.block[2] * c->geom.block[3];
 }
 
-// sites of one parity per lane pair (Vb even: Vb / 2 sites of each parity)
+// sites of one parity per lane pair (Vb even: Vb / 2 sites of each parity), and the threads that cover
+// a parity in as many equal passes
 static int eomr_k(const Ctx *c) {
-    const int nq = c->part_threads / 2, nh = eomr_vb(c) / 2;
-    return (nh + nq - 1) / nq;
+    const int nq = 32 * EOMR_WAVES;
+    return (eomr_vb(c) / 2 + nq - 1) / nq;
+}
+static int eomr_threads(const Ctx *c) {
+    const int nq = (eomr_vb(c) / 2 + eomr_k(c) - 1) / eomr_k(c);
+    return (2 * nq + 63) / 64 * 64;
 }
 
 bool eomr_supported(const Ctx *c, std::string &why) {
@@ -250,8 +266,7 @@ bool eomr_supported(const Ctx *c, std::string &why) {
         why = "the even-odd MR block solver needs a block whose vector fits one workgroup's LDS";
         return false;
     }
-    if (c->part_threads > 64 * EOMR_WAVES || c->part_threads % 64 || eomr_k(c) > EOMR_MAXK ||
-        c->parts_lds + 3 * EOMR_WAVES * sizeof(double) > 160 * 1024) {
+    if (eomr_vb(c) / 2 > EOMR_MAX_SITES || c->parts_lds + 3 * EOMR_WAVES * sizeof(double) > 160 * 1024) {
         why = "block too large for the even-odd MR block solver";
         return false;
     }
@@ -270,7 +285,7 @@ void launch_sap_phase_eomr(Ctx *c, int colour, int gather, int first, int ssor_o
     a.pnb = c->part_nb;
     a.gnb = c->part_gnb;
     a.pstart = c->part_pstart;
-    const dim3 grid(c->g.NBc), block(c->part_threads);
+    const dim3 grid(c->g.NBc), block(eomr_threads(c));
     const int K = eomr_k(c);
     INNER_SWITCH(c->prm.prec_inner, ({
                      using S2 = typename Prec<P_>::S2;
@@ -280,10 +295,8 @@ void launch_sap_phase_eomr(Ctx *c, int colour, int gather, int first, int ssor_o
                          k_sap_phase_eomr<P_, 1><<<grid, block, c->parts_lds, c->stream>>>(c->g, a, rs, rr, xx, yy, Uc, Fc);
                      else if (K == 2)
                          k_sap_phase_eomr<P_, 2><<<grid, block, c->parts_lds, c->stream>>>(c->g, a, rs, rr, xx, yy, Uc, Fc);
-                     else if (K == 3)
-                         k_sap_phase_eomr<P_, 3><<<grid, block, c->parts_lds, c->stream>>>(c->g, a, rs, rr, xx, yy, Uc, Fc);
                      else
-                         k_sap_phase_eomr<P_, 4><<<grid, block, c->parts_lds, c->stream>>>(c->g, a, rs, rr, xx, yy, Uc, Fc);
+                         k_sap_phase_eomr<P_, 3><<<grid, block, c->parts_lds, c->stream>>>(c->g, a, rs, rr, xx, yy, Uc, Fc);
                  }));
 }
 
@@ -291,8 +304,8 @@ int set_eomr_lds_limit(Ctx *c) {
     if (!c->use_parts || c->parts_lds <= 65536) return 0;
     const int bytes = (int)c->parts_lds;
     INNER_SWITCH(c->prm.prec_inner, ({
-                     const void *fn[4] = {(const void *)k_sap_phase_eomr<P_, 1>, (const void *)k_sap_phase_eomr<P_, 2>,
-                                          (const void *)k_sap_phase_eomr<P_, 3>, (const void *)k_sap_phase_eomr<P_, 4>};
+                     const void *fn[3] = {(const void *)k_sap_phase_eomr<P_, 1>, (const void *)k_sap_phase_eomr<P_, 2>,
+                                          (const void *)k_sap_phase_eomr<P_, 3>};
                      for (const void *f : fn) (void)hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
                  }));
     return hipGetLastError() == hipSuccess ? 0 : -1;

@@ -46,3 +46,23 @@ def test_phase_parity(orc, L, B, S, omega, prec):
     y, dy = (to_host(t) for t in s.sap_precondition(to_dev(v)))
     check_close(y, y_w, tm, "M_SAP")
     check_close(dy, dy_w, tm, "D M_SAP")
+
+
+# the even-odd MR kernel's passes over a parity: the largest block of one pass (384 sites of a
+# parity), the smallest sizes past it, the largest of two passes (768) and one of three
+@pytest.mark.parametrize("B", [(4, 6, 4, 8), (4, 4, 7, 7), (4, 6, 8, 8), (5, 6, 7, 8)], ids=lambda B: "x".join(map(str, B)))
+def test_eomr_passes(orc, B):
+    from paper_1210_7398_amd import sapq
+
+    L, kappa = tuple(2 * b for b in B), 0.125
+    print(L, B, flush=True)
+    U = synth.gauge_field(L, 0.25, 11)
+    F = synth.clover_inverse(L, U, 1.0, kappa)
+    s = sapq.Solver(L, B, (0, 0, 0, 0), kappa, n_sap=2, block_solver="eomr")
+    s.load_gauge(to_dev(U))
+    s.load_clover(to_dev(F))
+    v = synth.gaussian_spinor(L, 303)
+    y_w, dy_w = orc.msap(L, B, (0, 0, 0, 0), U, F, orc.params(kappa, n_sap=2, block_solver=1), v)
+    y, dy = (to_host(t) for t in s.sap_precondition(to_dev(v)))
+    check_close(y, y_w, 2e-5, "EO-MR M_SAP")
+    check_close(dy, dy_w, 2e-5, "EO-MR D M_SAP")
