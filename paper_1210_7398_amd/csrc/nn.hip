@@ -148,6 +148,18 @@ __device__ __forceinline__ void nn_link(cx<float> u[9], const float2 *__restrict
     }
 }
 
+// t = the transport of p along direction d: u times p's colour vectors (p itself for d = 0)
+__device__ __forceinline__ void nn_apply(cx<float> t[12], const cx<float> p[12], const cx<float> u[9], int d) {
+#pragma unroll
+    for (int be = 0; be < 4; ++be) {
+        const cx<float> h[3] = {p[3 * be], p[3 * be + 1], p[3 * be + 2]};
+        cx<float> o[3] = {h[0], h[1], h[2]};
+        if (d) su3_mul(o, u, h, false);
+#pragma unroll
+        for (int a = 0; a < 3; ++a) t[3 * be + a] = o[a];
+    }
+}
+
 // (T_d f[c])(ib, s) for channel c of an nch-channel activation, the neighbour (nb, ns) of
 // (ib, s) for d already known
 template <int RT>
@@ -160,13 +172,7 @@ __device__ __forceinline__ void nn_transport(cx<float> t[12], const float2 *__re
     cx<float> p[12], u[9];
     load_chan<RT>(p, f, nch, g, nb, ns, c);
     nn_link(u, L, (long)ib * g.Vb + s, d);
-#pragma unroll
-    for (int be = 0; be < 4; ++be) {
-        cx<float> h[3] = {p[3 * be], p[3 * be + 1], p[3 * be + 2]}, o[3];
-        su3_mul(o, u, h, false);
-#pragma unroll
-        for (int a = 0; a < 3; ++a) t[3 * be + a] = o[a];
-    }
+    nn_apply(t, p, u, d);
 }
 
 // (T_d in)(ib, s) for a one-channel input in the solver's layout and storage type S2
@@ -678,7 +684,7 @@ __global__ void __launch_bounds__(256) k_nn_layer1_mfma(GeomDev g, const typenam
 // the neighbour's record as one contiguous 768-byte piece.  The MFMA consumes the chunk from
 // LDS before the next one; the accumulators stay in registers.
 template <int COUT, int RT, int POUT>
-__global__ void __launch_bounds__(256, 4) k_nn_layer8_mfma(GeomDev g, const float2 *__restrict__ in,
+__global__ void __launch_bounds__(256, 3) k_nn_layer8_mfma(GeomDev g, const float2 *__restrict__ in,
                                                        void *__restrict__ out, const short4_t *__restrict__ Afrag,
                                                        const float2 *__restrict__ L, const int *__restrict__ skip) {
     if (skip && *skip) return;
@@ -708,17 +714,30 @@ __global__ void __launch_bounds__(256, 4) k_nn_layer8_mfma(GeomDev g, const floa
 #pragma unroll
     for (int j = 0; j < WT::N; ++j) acc[j] = float4_t{0.f, 0.f, 0.f, 0.f};
     __syncthreads();
-    // unrolled, so that both transports of a chunk have their loads in flight together
+    // A chunk's records and links are loaded while the chunk before it is in the matrix cores: three
+    // waves a SIMD instead of four with 8 channels out, and still 600 instead of 637 us at
+    // 24^3x48 (one channel out: no difference, 478).  The transports' vector arithmetic (1150 of
+    // 1840 instructions) and the address unit are then each busy a good half of the time.
+    cx<float> p[2][12], u[2][9];
+    auto fetch = [&](int dd, int dir) {
+        if (dir > 8) return;
+        load_chan<RT>(p[dd], in, CIN, g, dir == 0 ? ib : nb_blk[dir][t], dir == 0 ? s : nb_slot[dir][t], c);
+        if (dir > 0) nn_link(u[dd], L, (long)ib * g.Vb + s, dir);
+    };
+    fetch(0, 0);
+    fetch(1, 1);
 #pragma unroll
     for (int d0 = 0; d0 < 9; d0 += 2) {
         const int nd = d0 == 8 ? 1 : 2;
-        cx<float> T[2][12];
+        cx<float> T[12];
 #pragma unroll
         for (int dd = 0; dd < 2; ++dd)
-            if (dd < nd) nn_transport<RT>(T[dd], in, CIN, g, L, ib, s, d0 + dd, c, nb_blk[d0 + dd][t], nb_slot[d0 + dd][t]);
-#pragma unroll
-        for (int dd = 0; dd < 2; ++dd)
-            if (dd < nd) nn_put_b<BPAD>(Bt, t, (dd * CIN + c) * 4, 64 + (dd * CIN + c) * 4, T[dd]);
+            if (dd < nd) {
+                nn_apply(T, p[dd], u[dd], d0 + dd);
+                nn_put_b<BPAD>(Bt, t, (dd * CIN + c) * 4, 64 + (dd * CIN + c) * 4, T);
+            }
+        fetch(0, d0 + 2);
+        fetch(1, d0 + 3);
         __syncthreads();
         // k-tiles of the chunk: re rows of d0 (global tile 2 d0 + lt), im rows (K / 16 + 2 d0 + lt)
 #pragma unroll
