@@ -392,7 +392,8 @@ int sapq_defect_errors(sapq_ctx *ctx, float *e, const double *b, const double *x
  * The SAP phase kernel a context runs, chosen at creation from the block and the device's
  * LDS: 0 four lanes per site and one workgroup per block (the SSOR iterate in LDS, or in a
  * global scratch when it does not fit); 1 two lanes per site (forward / backward hops), one
- * workgroup per block, iterate in LDS; 2 two lanes per site with the block split along t into
+ * workgroup per block, iterate in LDS (four lanes where a workgroup has a CU to itself, one in
+ * 16-bit storage in the even-odd order); 2 two lanes per site with the block split along t into
  * two workgroups that exchange their boundary layers.  -1 for a null context.
  */
 int sapq_phase_kernel(const sapq_ctx *ctx);
