@@ -32,7 +32,8 @@ struct BField {
     GeomDev g;
     const void *Uin, *Fin;
     const double2 *U64, *F64;
-    float kappa, omega;
+    double kappa64;       // kappa of the FP64 residual
+    float kappa, omega;   // of the inner solve
     int n_ssor;
     int nrhs, rhs0;       // right-hand sides of this field and the index of its first one
     int ngroups;          // groups of NR right-hand sides
@@ -492,7 +493,7 @@ __global__ void __launch_bounds__(2 * BRES_SITES, 2) k_bresid(const BatchDev *__
     const int bl = (int)(i / g.Vb), s = (int)(i - (long)bl * g.Vb), ib = g.lex_blk[bl];
     const size_t ko = (size_t)k * F.nvec;
     const double2 *x = F.dv[DV_X] + ko, *U = F.U64;
-    const double sg = d ? -1.0 : 1.0, kappa = (double)F.kappa;
+    const double sg = d ? -1.0 : 1.0, kappa = F.kappa64;
     cx<double> acc[12];
     hop_any<0>(acc, g, x, U, ib, s, d, sg);
     hop_any<1>(acc, g, x, U, ib, s, d, sg);
@@ -955,6 +956,7 @@ static int setup_batch(Batch &B, sapq_ctx *const *ctxs, int nctx, const int *nrh
         F.Fin = c->Fin;
         F.U64 = c->U64;
         F.F64 = c->F64;
+        F.kappa64 = c->prm.kappa;
         F.kappa = (float)c->prm.kappa;
         F.omega = (float)c->prm.omega;
         F.n_ssor = c->prm.n_ssor;
