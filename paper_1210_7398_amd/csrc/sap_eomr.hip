@@ -252,6 +252,11 @@ static int eomr_threads(const Ctx *c) {
     return (2 * nq + 63) / 64 * 64;
 }
 
+// a block whose iterate and sums fit one workgroup's LDS
+static bool eomr_fits(const Ctx *c) {
+    return eomr_vb(c) / 2 <= EOMR_MAX_SITES && c->parts_lds + 3 * EOMR_WAVES * sizeof(double) <= 160 * 1024;
+}
+
 bool eomr_supported(const Ctx *c, std::string &why) {
     const sapq_geom &G = c->geom;
     if (G.subblock[0] || G.subblock[1] || G.subblock[2] || G.subblock[3]) {
@@ -266,7 +271,7 @@ bool eomr_supported(const Ctx *c, std::string &why) {
         why = "the even-odd MR block solver needs a block whose vector fits one workgroup's LDS";
         return false;
     }
-    if (eomr_vb(c) / 2 > EOMR_MAX_SITES || c->parts_lds + 3 * EOMR_WAVES * sizeof(double) > 160 * 1024) {
+    if (!eomr_fits(c)) {
         why = "block too large for the even-odd MR block solver";
         return false;
     }
@@ -300,8 +305,10 @@ void launch_sap_phase_eomr(Ctx *c, int colour, int gather, int first, int ssor_o
                  }));
 }
 
+// A context whose block this kernel cannot take needs no limit for it: the sums would not fit beside the
+// iterate of the largest blocks, and the refusal would be the context's.
 int set_eomr_lds_limit(Ctx *c) {
-    if (!c->use_parts || c->parts_lds <= 65536) return 0;
+    if (!c->use_parts || c->sap_np != 1 || !eomr_fits(c) || c->parts_lds <= 65536) return 0;
     const int bytes = (int)c->parts_lds;
     INNER_SWITCH(c->prm.prec_inner, ({
                      const void *fn[3] = {(const void *)k_sap_phase_eomr<P_, 1>, (const void *)k_sap_phase_eomr<P_, 2>,
