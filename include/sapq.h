@@ -106,7 +106,7 @@ typedef struct {
  * 2 n_ssor minimal-residual steps from 0 (the cost of n_ssor symmetric SSOR sweeps), then
  * x_o = v_o + K_oe x_e.  Needs the even-odd site order (subblock {0, 0, 0, 0}), an even
  * number of sites per block and a block whose vector fits one workgroup's LDS (96 bytes per
- * site: at most 1700 sites in gfx950's 160 KiB) (sapq_create: SAPQ_ESHAPE; sapq_set_params:
+ * site: at most 1698 sites in gfx950's 160 KiB) (sapq_create: SAPQ_ESHAPE; sapq_set_params:
  * SAPQ_EINVAL).  omega is unused.  sapq_autotune and sapq_solve_batch refuse such a context
  * (SAPQ_EINVAL). */
 #define SAPQ_FLAG_EOMR 16

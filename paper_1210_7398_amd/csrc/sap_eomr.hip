@@ -30,7 +30,7 @@ struct EomrArgs {
     const int *pstart;  // [0] = 0, [1] = Ve, [2] = Vb
 };
 
-constexpr int EOMR_MAX_SITES = 1024;  // of one parity in a block
+constexpr int EOMR_MAX_SITES = 849;  // of one parity in a block: its iterate and the sums in 160 KB of LDS
 constexpr int EOMR_WAVES = 12;        // at most 768 threads
 
 // sums of a, b, c over the workgroup, the same values (same order) in every thread

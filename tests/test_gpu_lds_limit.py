@@ -1,6 +1,6 @@
 """Blocks at the limit of a workgroup's LDS (160 KB): the largest iterates that the two-lane phase
 kernel holds, whole and split, which a context has to accept although the even-odd MR kernel's
-sums no longer fit beside them.
+sums no longer fit beside them, and the largest block of that kernel with the first it refuses.
 Tolerances: FP32 2e-5 (its roundings through n_sap 2), FP16 those of the M_SAP chain (3 unit roundoffs)."""
 import pytest
 
@@ -41,3 +41,11 @@ def _msap(orc, B, S, prec, tol, block_solver="ssor"):
 @pytest.mark.parametrize("B, S, kernel", CASES, ids=lambda p: "x".join(map(str, p)) if isinstance(p, tuple) else None)
 def test_largest_blocks(orc, B, S, kernel, prec, tol):
     assert _msap(orc, B, S, prec, tol).phase_kernel == kernel
+
+
+def test_largest_block_of_the_mr_solver(orc):
+    from paper_1210_7398_amd import sapq
+
+    _msap(orc, (2, 3, 1, 283), EO, "fp32", 2e-5, "eomr")  # 1698 sites
+    with pytest.raises(sapq.SapqError, match="block too large"):
+        sapq.Solver((10, 8, 10, 34), (5, 4, 5, 17), EO, 0.125, block_solver="eomr")  # 1700
