@@ -378,8 +378,9 @@ static void *beo_kernel(int prec, int Vb) {
     return prec == SAPQ_FP16 ? beo_kernel<SAPQ_FP16>(eo_class(Vb)) : beo_kernel<SAPQ_BF16>(eo_class(Vb));
 }
 
-// allow the batched phase kernels the dynamic LDS they are launched with
-static void batch_lds_attr(int bytes) {
+// allow the batched phase kernels the dynamic LDS they are launched with: all that any batch may
+// ask for, since the limit is the kernel's and not the batch's
+static bool batch_lds_attr(int bytes) {
     const void *fns[] = {
         (const void *)k_bsap_phase<SAPQ_FP32, 1>,    (const void *)k_bsap_phase<SAPQ_FP32, 2>,
         (const void *)k_bsap_phase<SAPQ_FP32, 3>,    (const void *)k_bsap_phase<SAPQ_FP32, 4>,
@@ -393,7 +394,9 @@ static void batch_lds_attr(int bytes) {
         (const void *)k_bsap_phase_2l<SAPQ_FP16, 3>, (const void *)k_bsap_phase_2l<SAPQ_FP16, 4>,
         (const void *)k_bsap_phase_2l<SAPQ_BF16, 1>, (const void *)k_bsap_phase_2l<SAPQ_BF16, 2>,
         (const void *)k_bsap_phase_2l<SAPQ_BF16, 3>, (const void *)k_bsap_phase_2l<SAPQ_BF16, 4>};
-    for (const void *f : fns) (void)hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+    bool ok = true;
+    for (const void *f : fns) ok = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, bytes) == hipSuccess && ok;
+    return ok;
 }
 
 // r_c += kappa F sum_{hops leaving the block} H x for every field and right-hand side
@@ -938,12 +941,13 @@ static int setup_batch(Batch &B, sapq_ctx *const *ctxs, int nctx, const int *nrh
     if (B.eo) {
         B.threads = eo_tables(c0).T;
         B.lds = eo_lds_bytes(c0->g.Vb, B.threads);
-        if (B.lds > 65536)
-            (void)hipFuncSetAttribute(beo_kernel(B.prec, c0->g.Vb), hipFuncAttributeMaxDynamicSharedMemorySize, (int)B.lds);
     }
-    if (B.lds > 65536) {
-        batch_lds_attr((int)B.lds);
+    if (B.lds > 65536 && !(B.eo ? hipFuncSetAttribute(beo_kernel(B.prec, c0->g.Vb), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                                      eo_lds_limit(c0->g.Vb)) == hipSuccess
+                                : batch_lds_attr(max_lds))) {
         (void)hipGetLastError();  // clears the runtime's last-error slot
+        why = "hipFuncSetAttribute refused the LDS size of the batched SAP kernel";
+        return SAPQ_EHIP;
     }
     if (c0->ssor_threads > 512) { why = "hyperplanes too large for the batched kernel"; return SAPQ_ESHAPE; }
     memset(&B.host, 0, sizeof(B.host));

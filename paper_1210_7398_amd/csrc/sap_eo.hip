@@ -64,8 +64,7 @@ void launch_sap_phase_eo(Ctx *c, int colour, bool gather, bool first, bool last,
 
 int set_eo_lds_limit(Ctx *c) {
     if (c->prm.prec_inner == SAPQ_FP32) return 0;
-    const int cls = eo_class(c->g.Vb), bytes = (int)eo_lds_bytes(EO_NS[cls] - 2, (EO_NS[cls] - 2) / 2);
-    (void)hipFuncSetAttribute(eo_kernel(c), hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+    (void)hipFuncSetAttribute(eo_kernel(c), hipFuncAttributeMaxDynamicSharedMemorySize, eo_lds_limit(c->g.Vb));
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 

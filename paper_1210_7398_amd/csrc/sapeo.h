@@ -49,6 +49,11 @@ constexpr int EO_THREADS = 512;  // at two waves per SIMD, which 256 registers a
 constexpr int EO_NS[3] = {258, 514, 1026};
 inline int eo_class(int Vb) { return Vb + 2 <= EO_NS[0] ? 0 : Vb + 2 <= EO_NS[1] ? 1 : 2; }
 inline size_t eo_lds_bytes(int Vb, int T) { return (size_t)96 * EO_NS[eo_class(Vb)] + (size_t)96 * T; }
+// the most that any block of Vb's pitch takes: the limit to set for the kernel they share
+inline int eo_lds_limit(int Vb) {
+    const int most = EO_NS[eo_class(Vb)] - 2;
+    return (int)eo_lds_bytes(most, most / 2);
+}
 
 __device__ __forceinline__ unsigned raw2(__half2 v) { return *reinterpret_cast<unsigned *>(&v); }
 __device__ __forceinline__ unsigned raw2(__hip_bfloat162 v) { return *reinterpret_cast<unsigned *>(&v); }
