@@ -63,9 +63,11 @@ void launch_sap_phase_eo(Ctx *c, int colour, bool gather, bool first, bool last,
 }
 
 int set_eo_lds_limit(Ctx *c) {
-    if (c->prm.prec_inner == SAPQ_FP32) return 0;
-    (void)hipFuncSetAttribute(eo_kernel(c), hipFuncAttributeMaxDynamicSharedMemorySize, eo_lds_limit(c->g.Vb));
-    return hipGetLastError() == hipSuccess ? 0 : -1;
+    const int bytes = eo_lds_limit(c->g.Vb);
+    if (c->prm.prec_inner == SAPQ_FP32 || bytes <= 65536) return 0;
+    if (hipFuncSetAttribute(eo_kernel(c), hipFuncAttributeMaxDynamicSharedMemorySize, bytes) == hipSuccess) return 0;
+    (void)hipGetLastError();  // clears the runtime's last-error slot
+    return -1;
 }
 
 }  // namespace sapq
