@@ -177,9 +177,10 @@ static int check_params(const sapq_params *p, std::string &why) {
     return SAPQ_OK;
 }
 
-static int upload_parts(Ctx *c, const HostTables &T, const PartTables &PT) {
-    EoHostTables E;
-    build_eo(T, E);
+// The tables of the two-lane kernels, and those of the one-lane kernel where the order and precision
+// can take it.  The caller keeps PT and E until it has synchronized the stream.
+static int upload_parts(Ctx *c, const sapq_geom *G, const HostTables &T, const PartTables &PT, EoHostTables &E) {
+    if (c->sap_np == 1 && eo_order(G) && c->prec_created != SAPQ_FP32) build_eo(T, E);
     struct { void *dst; const void *src; size_t bytes; } cp[] = {
         {c->part_gslot, PT.gslot.data(), PT.gslot.size() * sizeof(int)},
         {c->part_pstart, PT.pstart.data(), PT.pstart.size() * sizeof(int)},
@@ -191,10 +192,11 @@ static int upload_parts(Ctx *c, const HostTables &T, const PartTables &PT) {
         {c->eo_nb, E.nb.data(), E.nb.size() * sizeof(unsigned)},
         {c->eo_face, E.face.data(), E.face.size() * sizeof(unsigned)}};
     for (auto &e : cp) {
+        if (!e.bytes) continue;
         int rc = hipcheck(hipMemcpyAsync(e.dst, e.src, e.bytes, hipMemcpyHostToDevice, c->stream), "hipMemcpyAsync(part tables)");
         if (rc) return rc;
     }
-    return hipcheck(hipStreamSynchronize(c->stream), "hipStreamSynchronize");  // E lives until here
+    return SAPQ_OK;
 }
 
 // The two workgroups of a block wait on each other with a bounded spin; a time-out (or a
@@ -367,8 +369,9 @@ int sapq_create(const sapq_geom *geom, const sapq_params *params, void *arena, s
                       "hipMemcpyAsync(tables)");
         if (rc) { hipHostFree(c->host_res); delete h; return rc; }
     }
+    EoHostTables ET;
     if (c->use_parts) {
-        rc = upload_parts(c, T, PT);
+        rc = upload_parts(c, geom, T, PT, ET);
         if (rc == SAPQ_OK)
             rc = hipcheck(hipMemsetAsync(c->xch, 0, (size_t)c->g.NBc * PT.NP * 3 * 24 * std::max(PT.Hp, 1) * 8, c->stream),
                           "hipMemsetAsync(halo)");
@@ -1090,12 +1093,13 @@ static int apply_subblock(Ctx *c, const int S[4]) {
     HostTables T;
     build_tables(&G, T);
     PartTables PT;
+    EoHostTables ET;
     if (c->use_parts) {
         if (T.nplanes > MAX_PLANES || !build_parts(&G, T, c->sap_np, PT) || PT.Hp != c->part_Hp) {
             set_error("sub-block shape does not fit the split of the block");
             return SAPQ_ESHAPE;
         }
-        rc = upload_parts(c, T, PT);
+        rc = upload_parts(c, &G, T, PT, ET);
         if (rc) return rc;
     } else if (T.nplanes > MAX_PLANES || T.max_plane * 4 > 512) {
         set_error("sub-block shape gives too large a hyperplane");
