@@ -228,9 +228,7 @@ static void use_fp32_storage(Ctx *c, bool on) {
     c->prm.prec_inner = on ? SAPQ_FP32 : c->prec_created;
 }
 
-constexpr int N_CU = 256;  // compute units of an MI355X
-
-static size_t plan(const sapq_geom *geom, const sapq_params *prm, Ctx *c, HostTables &T, PartTables &PT, int max_lds) {
+static size_t plan(const sapq_geom *geom, const sapq_params *prm, Ctx *c, HostTables &T, PartTables &PT, int max_lds, int n_cu) {
     build_tables(geom, T);
     c->geom = *geom;
     c->prm = *prm;
@@ -276,11 +274,7 @@ static size_t plan(const sapq_geom *geom, const sapq_params *prm, Ctx *c, HostTa
             c->part_threads = std::min(512, std::max(64, ((2 * PT.max_plane + 63) / 64) * 64));
             c->parts_lds = lds;
             c->part_max_plane = PT.max_plane;
-            // one workgroup of the phase kernel per CU: by its LDS (a gfx950 workgroup may take all of
-            // its CU's), or a whole block's by their number (of one colour)
-            long blocks = 1;
-            for (int mu = 0; mu < 4; ++mu) blocks *= geom->L[mu] / geom->block[mu];
-            c->parts_alone = (long)lds > (long)max_lds / 2 || (np == 1 && blocks / 2 <= N_CU);
+            c->parts_alone = alone_on_cu(geom, np, lds, (size_t)max_lds, n_cu);
             c->ssor_staged = false;
         }
     }
@@ -305,6 +299,12 @@ static int device_max_lds() {
     return v;
 }
 
+static int device_cus() {
+    int dev = 0, v = 256;  // an MI355X
+    if (hipGetDevice(&dev) == hipSuccess) (void)hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev);
+    return v;
+}
+
 size_t sapq_arena_bytes(const sapq_geom *geom, const sapq_params *params) {
     std::string why;
     if (!geom || !params || check_geom(geom, why) != SAPQ_OK || check_params(params, why) != SAPQ_OK) return 0;
@@ -313,8 +313,8 @@ size_t sapq_arena_bytes(const sapq_geom *geom, const sapq_params *params) {
     Ctx c0{}, c1{};
     HostTables T0, T1;
     PartTables P0, P1;
-    const size_t a = plan(geom, params, &c0, T0, P0, 0);
-    const size_t b = plan(geom, params, &c1, T1, P1, std::max(device_max_lds(), 160 * 1024));
+    const size_t a = plan(geom, params, &c0, T0, P0, 0, device_cus());
+    const size_t b = plan(geom, params, &c1, T1, P1, std::max(device_max_lds(), 160 * 1024), device_cus());
     return std::max(a, b);
 }
 
@@ -330,7 +330,7 @@ int sapq_create(const sapq_geom *geom, const sapq_params *params, void *arena, s
     Ctx *c = &h->c;
     HostTables T;
     PartTables PT;
-    size_t need = plan(geom, params, c, T, PT, device_max_lds());
+    size_t need = plan(geom, params, c, T, PT, device_max_lds(), device_cus());
     if (T.max_plane > 4096 || T.Vb > 32767) { delete h; set_error("block too large"); return SAPQ_ESHAPE; }
     if ((long)c->lds_extra > (long)device_max_lds()) { delete h; set_error("block too large for LDS tables"); return SAPQ_ESHAPE; }
     if (T.nplanes > MAX_PLANES) { delete h; set_error("too many hyperplanes"); return SAPQ_ESHAPE; }

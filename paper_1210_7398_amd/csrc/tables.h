@@ -288,6 +288,15 @@ inline bool build_parts(const sapq_geom *G, const HostTables &T, int NP, PartTab
     return true;
 }
 
+// Whether a workgroup of the phase kernel has a CU to itself: by its LDS (a gfx950 workgroup may
+// take all of its CU's), or a whole block's by the number of blocks of a colour on a device, or a
+// partition of one, of n_cu CUs.
+inline bool alone_on_cu(const sapq_geom *G, int NP, size_t lds, size_t max_lds, int n_cu) {
+    long blocks = 1;
+    for (int m = 0; m < 4; ++m) blocks *= G->L[m] / G->block[m];
+    return lds > max_lds / 2 || (NP == 1 && blocks / 2 <= n_cu);
+}
+
 // Tables of the one-lane even-odd phase kernel: per slot the LDS slots of the eight in-block
 // neighbours +x -x +y -y ... (two per word; Vb, the zero slot, for one outside the block), and per
 // direction the Vb / B[mu] sites of its forward face and then those of its backward one, each
