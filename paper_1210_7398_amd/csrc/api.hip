@@ -253,7 +253,7 @@ static size_t plan(const sapq_geom *geom, const sapq_params *prm, Ctx *c, HostTa
     // SAPQ_HALO_TIMEOUT_TEST=1 (read here) makes every wait of a split block on its partner's
     // halo words time out after 64 polls, so that the time-out path (error flag, SAPQ_EHIP)
     // can be tested with every kernel still running to its end
-    c->halo_spin_limit = 1 << 20;
+    c->halo_spin_limit = HALO_SPIN_LIMIT;
     c->halo_wait_xor = 0;
     if (const char *e = getenv("SAPQ_HALO_TIMEOUT_TEST"))
         if (atoi(e) == 1) {

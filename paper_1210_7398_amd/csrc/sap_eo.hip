@@ -26,16 +26,17 @@ EoTables eo_tables(const Ctx *c) {
 }
 
 // The rule: the even-odd site order at omega = 1 in a 16-bit storage precision (whose links and
-// clover blocks fit the registers of one lane), blocks of two or more sites in every direction
-// (so that the two faces of a direction share no site), more than EO_MIN_SITES sites and at most
-// EO_THREADS threads.  Every other phase keeps the kernels that reload a site's links: at omega != 1
-// the turn planes change, FP32 fields would take twice the registers, and a small block is one wave,
-// partly idle, with 31 KB of LDS, of which a CU holds five.  Measured, a SAP cycle in FP16, here and with the two-lane or four-lane form: 2x2x2x4 blocks 1079 and 494 us
-// (14112 of a colour), 2x2x4x4 594 and 396 (7200), 2x3x4x4 197 and 176 (1536) but 455 and 469 (5000),
-// 3x3x3x4 144 and 154 (1152), 2x4x4x4 319 and 364 (3200), 4^4 297 and 403 (2048), 4x4x4x8 519 and
-// 811 (2048), 4x4x6x6 1102 and 1024 (2048; BF16 953 and 1432), 4x4x8x8 636 and 919 (1024).
-// With few blocks (up to 256 of a colour, four lanes per site) 4x4x4x6 85 and 104, 4^4 79 and 80
-// (BF16 83 and 75), 2x4x4x4 81 and 59.
+// clover blocks fit the registers of one lane), blocks of two or more sites in every direction (so
+// that the two faces of a direction share no site), more than EO_MIN_SITES sites and at most
+// EO_THREADS threads.  Every other phase keeps the kernels that reload a site's links: at omega !=
+// 1 the turn planes change, FP32 fields would take twice the registers, and a small block is one
+// wave, partly idle, with 31 KB of LDS, of which a CU holds five.  Measured, a SAP cycle in FP16,
+// here and with the two-lane or four-lane form: 2x2x2x4 blocks 1079 and 494 us (14112 of a colour),
+// 2x2x4x4 594 and 396 (7200), 2x3x4x4 197 and 176 (1536) but 455 and 469 (5000), 3x3x3x4 144 and
+// 154 (1152), 2x4x4x4 319 and 364 (3200), 4^4 297 and 403 (2048), 4x4x4x8 519 and 811 (2048),
+// 4x4x6x6 1102 and 1024 (2048; BF16 953 and 1432), 4x4x8x8 636 and 919 (1024). With few blocks (up
+// to 256 of a colour, four lanes per site) 4x4x4x6 85 and 104, 4^4 79 and 80 (BF16 83 and 75),
+// 2x4x4x4 81 and 59.
 constexpr int EO_MIN_SITES = 96;
 bool eo_supported(const Ctx *c) {
     const int Vb = c->g.Vb, Ve = (Vb + 1) / 2, *B = c->geom.block;

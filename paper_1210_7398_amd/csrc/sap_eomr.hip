@@ -60,8 +60,9 @@ __device__ __forceinline__ void block_sum3(double &a, double &b, double &c, doub
 // those sites stay in registers across the steps).  What bounds it: the latency of a site's
 // loads and instructions, with the waves that the registers of an LDS-filled CU allow, and at
 // 24^3x48 memory.  Left alone the compiler keeps the tables and addresses of all K sites across
-// the steps (39 registers spilled at K = 3 and two waves a SIMD); with the site index opaque and the
-// sites kept apart, K = 2 fits three waves a SIMD.  M_SAP with 6^4 blocks at 24^3x48: FP32
+// the steps (39 registers spilled in FP32, 46 and 48 in FP16 and BF16, at K = 3 and two waves a SIMD);
+// with the site index opaque and the sites kept apart, K = 2 fits three waves a SIMD (2 registers
+// spilled in FP32, none in 16 bits).  M_SAP with 6^4 blocks at 24^3x48: FP32
 // 3640 -> 3279 us (eight waves without the spills 3345), FP16 2527 (eight waves) -> 2393; 4x6x4x8
 // blocks at 16^2x24x32, FP32, 1537 (eight waves) -> 1252.
 template <int P, int K>

@@ -8,8 +8,9 @@
 //
 // Lanes.  Lane d = 0 of a pair takes the four forward hops of its site, lane d = 1 the
 // four backward hops.  Both run the same instructions: the projection sign is s = +1 / -1,
-// and lane 1 reads U_mu at its backward neighbour and turns it into U^+ with selects (a
-// daggered copy of the links at the site would cost a quarter more bytes per sweep).  After
+// and lane 1 reads U_mu at its backward neighbour, transposes it with selects and works on
+// conjugates, whose signs ride on multiply-adds (a daggered copy of the links at the site would
+// cost a quarter more bytes per sweep).  After
 // the pair's sum each lane owns one chiral half (spins 2d and 2d + 1), applies its 6x6
 // block of F and updates those six components.
 //
@@ -26,19 +27,19 @@
 // on a part that is already running; the last workgroup resets the counter.
 //
 // What bounds it: the dependent chain of a hyperplane step (table entries, loads, LDS reads, about
-// 760 vector instructions of a site update per lane, LDS store, barrier), with one or two waves
-// a SIMD.  Cycle stamps of the 24^3x48 launch showed 2700 of a step's 13000 cycles outside the
+// 800 vector instructions of a site update per lane, LDS store, barrier), with one or two waves a
+// SIMD.  Cycle stamps of the 24^3x48 launch showed 2700 of a step's 13000 cycles outside the
 // update: every wave copied a share of the halo words (with integer divisions by their number),
-// read the hyperplane starts from LDS, and a pointer choice between LDS and global memory made
-// flat loads, after which every wait is for all loads in flight.  With a wave of its own for the
-// halo words, the starts in registers (v_readlane), record-wise LDS, the dagger of the backward
-// links folded into signs the instructions take anyway (902 -> 760) and no relaxation
-// arithmetic at omega = 1, a launch takes 458 us instead of 533 (FP32, 6^3x12 blocks, the same
-// bits), now 455: the L2 misses of its sweeps are 2.8 GB, 6.0 TB/s, what the card's memory gives, the
-// wide planes waiting on it while the narrow ones leave it idle (with every load an L2 hit it
-// would take 390).  Measured and not kept: a site's links, or all it needs, loaded a step ahead (507 us with
-// two hops' links, 10% slower than without once the waits were exact; all of it spills in FP32
-// and gains nothing in FP16).
+// read the hyperplane starts from LDS, and a pointer choice between LDS and global memory made flat
+// loads, after which every wait is for all loads in flight.  With a wave of its own for the halo
+// words, the starts in registers (v_readlane), record-wise LDS, the dagger of the backward links
+// folded into signs the instructions take anyway (902 -> 760, 798 in the present lane order) and no
+// relaxation arithmetic at omega = 1, a launch takes 458 us instead of 533 (FP32, 6^3x12 blocks,
+// the same bits), now 450 to 458.  Its requests leaving the L2s are 2.7 GB, 6.0 TB/s, which the
+// last-level cache and memory serve together (a colour's links, clover and v are 191 MB); with
+// every load an L2 hit it would take 390, so the chain is the larger part.  Measured and not kept:
+// a site's links, or all it needs, loaded a step ahead (507 us with two hops' links, 10% slower
+// than without once the waits were exact; all of it spills in FP32 and gains nothing in FP16).
 #include <algorithm>
 #include <type_traits>
 
@@ -64,8 +65,6 @@ struct PartArgs {
     unsigned wait_xor;        // 0; nonzero only where a test forces the time-out path (no
                               // written word then carries the awaited tag)
 };
-
-constexpr int SPIN_LIMIT = 1 << 20;  // default bounded wait on a halo word (about a second)
 
 __device__ __forceinline__ unsigned xch_tag(unsigned epoch, int sweep) {
     return 0x80000000u | ((epoch & 0x1ffffffu) << 6) | (unsigned)(sweep & 63);
@@ -101,7 +100,7 @@ __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(
 
 // ALONE: the workgroup has a CU to itself.  A whole block (NP = 1) then takes four lanes per site on the
 // hyperplanes that its waves hold that way, and up to 12 waves: on an idle CU a step lasts as long as
-// one wave's instructions and their latency (5900 cycles at 4^4 blocks, 760 instructions), and
+// one wave's instructions and their latency (5900 cycles at 4^4 blocks with two lanes), and
 // the wider planes need fewer passes.  Measured, M_SAP in FP32 unless said, two lanes -> four:
 // 4^4 blocks 813 -> 696 us (8 workgroups), 842 -> 733 (128), 963 -> 793 (256), but 1191 -> 1485
 // (384, where CUs are shared and issue slots are what is short: that kernel stays at

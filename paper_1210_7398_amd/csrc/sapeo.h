@@ -8,11 +8,15 @@
 // nothing but the neighbours' iterate in LDS, every lane has work in every half-update, and four
 // 4^4 blocks (of two waves) share a CU.  The two-lane kernel reloads links and clover rows in
 // every half-sweep (450 KB per 4^4 block, more than the L2 holds for the blocks in flight) and
-// needs 1.4 times the vector instructions per site (its lanes dagger links with selects, convert
-// and add two halves).  A phase at 32^3x64 in 4^4 blocks of FP16 took 538 us and takes 303: the
-// sweeps 147, at the rate of their 1340 vector instructions a site update (154 us at the 4.3
-// cycles each that two waves a SIMD reach), the gather, loads and outputs the rest, 432 bytes
-// per site at 4 TB/s.  One site per thread, with half the waves idle in each half-update, took 365.
+// needs 1.27 times the vector instructions per site in FP16 (two lanes of 848 against 1336: its
+// lanes transpose links with selects, both compute addresses, and add two halves).  A phase at 32^3x64
+// in 4^4 blocks of FP16 took 538 us and takes 303, 278 in the cycles between a call's first and last
+// (BF16 263).  From 4 to 8 SSOR iterations one adds 41 us (BF16 30), so the four take about 155:
+// bound by the issue of their vector instructions, of which FP16 has 864 v_fma_mix_f32 at 4.4
+// cycles and 472 plain ones at 2.7 (two waves a SIMD), BF16 1528 with 96 shifts at 4.4.  The other
+// 123 us are the first loads and the gather, the residual's half-update (20) and the outputs,
+// 432 bytes per site in all.  One site per thread, with half the waves idle in each half-update,
+// took 365.
 //
 // At omega = 1 the sweeps are 2 n_ssor half-updates o, e, o, e, ...: the first update of the even
 // sites from x = 0 gives x_e = v_e, and the plane at each turn of a sweep keeps its values.  After
@@ -80,9 +84,9 @@ __device__ __forceinline__ void lds_planar(cx<float> psi[12], const float4 *xs, 
 __device__ __forceinline__ void opaque(unsigned &w) { asm volatile("" : "+v"(w)); }
 
 // Products whose first factor comes from 16-bit storage.  The first product of a sum is a fused
-// multiply-add onto zero, not a multiply, so that the compiler can read the factor from its
-// 16-bit half (v_fma_mix_f32, full rate) instead of converting it: 84 of 1460 vector
-// instructions of a site update.
+// multiply-add onto zero, not a multiply, so that the compiler can read the factor from its FP16
+// half (v_fma_mix_f32) instead of converting it first: 1336 vector instructions a site update
+// instead of 1420.  (BF16 converts by shifts and masks, and has the same 1528 either way.)
 __device__ __forceinline__ cx<float> emul(cx<float> a, cx<float> b) {
     return {fmx(a.r, b.r, -fmx(a.i, b.i, 0.f)), fmx(a.r, b.i, fmx(a.i, b.r, 0.f))};
 }

@@ -228,6 +228,8 @@ struct Prof {
     int n[8] = {0};
 };
 
+constexpr int HALO_SPIN_LIMIT = 1 << 20;  // polls of a split block's bounded wait on a halo word (about a second)
+
 struct Ctx {
     sapq_geom geom;
     sapq_params prm;
@@ -263,7 +265,7 @@ struct Ctx {
     // fields
     double2 *U64, *F64;
     int *slot_perm;   // [Vb] staging of a slot re-ordering (sub-block change)
-    int halo_spin_limit = 1 << 20;  // polls of a split block's bounded wait on a halo word
+    int halo_spin_limit = HALO_SPIN_LIMIT;
     unsigned halo_wait_xor = 0;     // nonzero: every such wait times out (failure-path tests)
     void *Uin, *Fin;  // inner storage precision
     bool have_U, have_F;

@@ -96,12 +96,6 @@ enum { HOP_IN, HOP_OUT };  // hops inside the block, hops leaving it
 template <int CTRL> __device__ __forceinline__ float quad_get(float v) {
     return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, true));
 }
-template <int CTRL> __device__ __forceinline__ double quad_get(double v) {
-    long long b = __double_as_longlong(v);
-    int lo = __builtin_amdgcn_update_dpp(0, (int)(b & 0xffffffffLL), CTRL, 0xF, 0xF, true);
-    int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, 0xF, 0xF, true);
-    return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
-}
 constexpr int QUAD_XOR1 = 0xB1;  // quad_perm [1, 0, 3, 2]
 constexpr int QUAD_XOR2 = 0x4E;  // quad_perm [2, 3, 0, 1]
 
