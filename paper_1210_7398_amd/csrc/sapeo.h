@@ -20,8 +20,8 @@
 //
 // At omega = 1 the sweeps are 2 n_ssor half-updates o, e, o, e, ...: the first update of the even
 // sites from x = 0 gives x_e = v_e, and the plane at each turn of a sweep keeps its values.  After
-// the last one x_e = v_e + K_eo x_o, so the block residual of the even sites is zero and only the
-// odd sites' is computed.
+// the last one x_e = v_e + K_eo x_o, so the block residual of the even sites is zero (or x not finite)
+// and only the odd sites' is computed.
 //
 // The gather of the other colour runs over the block's faces, one direction pair at a time
 // (forward and backward faces of a direction share no site), into accumulators in LDS: a face of
@@ -411,9 +411,11 @@ __device__ __forceinline__ void eo_phase(const GeomDev &g, const EoTables &t, fl
     if (live_e) {
         finish(ye, se);
         if ((mode & (EO_LAST | EO_SSOR_ONLY)) == EO_LAST) {
+            // 0, and not a number where x is infinite or none, as v - A x would be
             cx<float> z[12];
+            lds_planar(z, xs, NS, se);
 #pragma unroll
-            for (int c = 0; c < 12; ++c) z[c] = cxz<float>();
+            for (int c = 0; c < 12; ++c) z[c] = z[c] - z[c];
             store_spinor(r, g, ib, se, z);
         }
     }
